@@ -229,7 +229,8 @@ def prepare(case, seed):
             U0 = _request_state(system, nx, ny, k, seed).cpu().numpy()
             probs.append(_problem(system, nx, ny, "zero_gradient", 0.4 if ny else 0.8, 1.0,
                                   2.0 if system == "mhd" else 1.4, steps, U0=U0))
-        return {"case": case, "problems": probs, "pool": vklb.Pool(512 << 20, case["precision"])}
+        return {"case": case, "problems": probs, "pool": vklb.Pool(512 << 20, case["precision"]),
+                "kept": [np.zeros(p.U0.shape, np.float32) for p in probs]}
     U0 = _state(case["system"], case["nx"], case["ny"], case["data"], case["gamma"], seed).contiguous()
     prob = _problem(case["system"], case["nx"], case["ny"], case["bc"], case["nu"], case["omega"], case["gamma"],
                     case["steps"], case["T"])
@@ -238,13 +239,16 @@ def prepare(case, seed):
         st["U"] = torch.empty_like(U0)
     else:
         st["solver"] = vklb.Solver(prob, precision=case["precision"])
+        st["kept"] = [np.zeros(tuple(U0.shape), np.float32)]
     return st
 
 
-def _kept(U, precision):
-    """Fields as the program keeps them: FP32 solves in FP32."""
-    U = torch.from_numpy(U) if isinstance(U, np.ndarray) else U
-    return U.to(torch.float32) if precision == "fp32" else U
+def _kept(U, state, k=0):
+    """Fields as the program keeps them: FP32 solves in FP32, in arrays of its own."""
+    if state["case"]["precision"] != "fp32":
+        return U
+    np.copyto(state["kept"][k], U, casting="same_kind")
+    return state["kept"][k]
 
 
 def run(state):
@@ -252,7 +256,7 @@ def run(state):
     prec = case["precision"]
     if case["path"] == "static":
         vklb.run_static(state["problem"], prec, case["steps"], state["U0"].data_ptr(), state["U"].data_ptr())
-        return {"U": _kept(state["U"], prec)}
+        return {"U": state["U"].to(torch.float32) if prec == "fp32" else state["U"]}
     if case["path"] == "pool":
         pool, probs = state["pool"], state["problems"]
         for k, p in enumerate(probs):
@@ -262,11 +266,11 @@ def run(state):
             pool.run(64)
             for c in pool.poll():
                 got[c["tag"]] = c["U"]
-        return [_kept(got[k], prec) for k in range(len(probs))]
+        return [_kept(got[k], state, k) for k in range(len(probs))]
     s = state["solver"]
     s.init_device(state["U0"].data_ptr())
     U, t, _ = s.run() if case["T"] else s.run(case["steps"])
-    return {"U": _kept(U, prec), "t": np.float32(t) if prec == "fp32" else np.float64(t)}
+    return {"U": _kept(U, state), "t": np.float32(t) if prec == "fp32" else np.float64(t)}
 
 
 def work(case):
