@@ -16,10 +16,11 @@ FP64, the 1D smooth wave to 65,536 cells, 1D and 2D MHD), and the mixed
 request stream under "serving".
 
 Prints one JSON line: value = cells x time steps / second (Mcell-steps/s) of
-the timed solves; roofline = algorithmic bytes of the step kernel (each
-population read once and written once, 2 Q p s bytes per cell-step, times
-the cells and steps of a launch) over its average launch duration, measured
-with HIP events on the solver's stream; cpu_baseline = the FP64 oracle on a
+the timed solves; roofline = algorithmic bytes of the step kernel (the stored
+state read once and written once: U, 2 p s bytes per cell-step, in 2D solves
+with omega = 1; every population, 2 Q p s, in the others; times the cells and
+steps of a launch) over its average launch duration, measured with HIP events
+on the solver's stream; cpu_baseline = the FP64 oracle on a
 bounded sample of the same workload.
 """
 from __future__ import annotations
@@ -65,14 +66,18 @@ def log(msg):
 
 
 def alg_bytes_per_cell_step(P, prec):
-    return 2 * P.Q * P.p * (4 if prec == "fp32" else 8)
+    """Bytes a cell-step cannot do without: the stored state read once and
+    written once. 2D solves with omega = 1 store U (the collision then returns
+    the equilibrium of U), the others every population."""
+    slots = 1 if P.dim == 2 and P.omega == 1.0 else P.Q
+    return 2 * slots * P.p * (4 if prec == "fp32" else 8)
 
 
 # Files that define the step kernels and their launch parameters (tile
 # shapes, bands, halo batches): a change to any of them makes earlier byte
 # counts stale. The runtime, the pool and the host cell check are not among
 # them.
-KERNEL_SOURCES = ("vklb_cell.hpp", "vklb_kernels.hpp", "vklb_launch.hpp", "vklb_host.hpp", "vklb_system.inc",
+KERNEL_SOURCES = ("vklb_cell.hpp", "vklb_kernels.hpp", "vklb_omega1.hpp", "vklb_launch.hpp", "vklb_host.hpp", "vklb_system.inc",
                   "k_sw.hip", "k_euler.hip", "k_mhd.hip", "k_linear.hip")
 
 
@@ -174,7 +179,7 @@ def step_kernel(P, steps):
     options); everything else launches k_step1d / k_step2d once per step."""
     if P.dim == 1 and P.cells <= (256 if P.system == "mhd" else 1024):
         return "k_run1d_wg", min(1024, steps)
-    return f"k_step{P.dim}d", 1
+    return ("k_ustep2d" if P.dim == 2 and P.omega == 1.0 else f"k_step{P.dim}d"), 1
 
 
 def time_workload(name, prec, K, W):
@@ -264,8 +269,8 @@ def serving_bench(count, seed=1, budget=None, sample_every=5):
             "mcell_steps_per_s", "alg_gb_per_s", "hbm_frac", "graph_launches", "graph_captures")
 
     def r(d):
-        # the stream's aggregate algorithmic bytes (2 Q p s per cell-step of
-        # every completed solve) over the makespan, as a fraction of 8 TB/s
+        # the stream's aggregate algorithmic bytes (the stored state of every
+        # completed solve's cells, read and written once per step) over the makespan, as a fraction of 8 TB/s
         d = dict(d, hbm_frac=d["alg_gb_per_s"] / 8000.0)
         return {k: (round(d[k], 4) if isinstance(d[k], float) else d[k]) for k in keep if k in d}
     log(f"serving: 2D tile shapes tuned in {tune_s:.1f} s")

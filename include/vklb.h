@@ -132,14 +132,21 @@ typedef struct {
                           an error-free sum, so U's rounding does not build up over many steps
                           (FP32 only; VKLB_ERR_ARG with FP64);
                        0: default: FP64 -> 1; FP32 -> 3 in 1D, 2 in 2D.
-                       Other values: VKLB_ERR_ARG. */
+                       Other values: VKLB_ERR_ARG.
+                       2D solves with omega = 1 keep U alone between steps (as their basis forms
+                       it: 1 the sum of the populations, 2 and 3 U plus differences), since the
+                       collision then returns the equilibrium of U; vklb_get_state rebuilds the
+                       populations of the basis. */
   int band_rows;    /* 2D: rows per workgroup band (MHD in the delta bases: at most 64, larger values
                        are taken as 64); 0 = the default: the tallest power of two from 512 down to
-                       4 rows that gives a step at least 2048 wavefronts (two per SIMD) */
+                       4 rows that gives a step at least 2048 wavefronts (two per SIMD); omega = 1:
+                       the fewest rows, 2 to 16 (MHD 32), that let every wavefront be resident */
   int graph_chunk;  /* steps captured per HIP graph (0 = 512; < 0: plain launches) */
   int strip_width;  /* 2D: columns per workgroup (64, 128 or 256); 1D: lanes per workgroup
-                       (256 or 512, each finishing W - 2 cells); 0 = tuned default */
-  int halo_rows;    /* 2D: rows of the two halo columns collided per batch (1..32); 0 = tuned default */
+                       (256 or 512, each finishing W - 2 cells); 0 = tuned default. 2D with omega = 1:
+                       always 64 columns per wavefront */
+  int halo_rows;    /* 2D: rows of the two halo columns collided per batch (1..32); 0 = tuned default;
+                       omega = 1: always 32 */
   int small_grid;   /* 1D grids of up to 1024 cells (256 for MHD), any boundary condition,
                        run up to 1024 steps per launch in one workgroup, with bitwise the same
                        results as one launch per step: 0 = on, 512 lanes (256 for MHD), the fastest
@@ -239,7 +246,7 @@ void vklb_destroy(vklb_solver* s);
  *  - 1D candidates: 256- or 512-lane workgroups; grids of up to 1024 cells
  *    (not MHD) that run in one workgroup: 256, 512 or 1024 lanes.
  *  - 2D candidates: strips of 64/128/256 columns, bands of 4..64 rows, halo
- *    batches of 2, 8, 16 or 32 rows.
+ *    batches of 2, 8, 16 or 32 rows (omega = 1: bands only).
  * All shapes give identical results, so the choice only affects speed. The
  * end condition is ignored while timing. Allocates one workspace
  * (vklb_workspace_bytes) for the duration of the call and synchronizes.

@@ -690,6 +690,20 @@ struct Equilibrium {
       fminus[v] = c * U[v] - Fm * ixi;
     }
   }
+
+  // The same, and F+ - F- of the axis (what the rest population gives up).
+  __host__ __device__ static void eval_axis_net(const S* U, const Phys& ph, S ixi, S Lam, S ch, int d, S* fplus,
+                                                S* fminus, S* net) {
+    const S c = S(ph.c);
+    S F[P], D[P];
+    C::split(d, U, ph, Lam, ch, F, D);
+    for (int v = 0; v < P; ++v) {
+      const S Fp = S(0.5) * F[v] + D[v], Fm = S(0.5) * F[v] - D[v];
+      fplus[v] = c * U[v] + Fp * ixi;
+      fminus[v] = c * U[v] - Fm * ixi;
+      net[v] = Fp - Fm;
+    }
+  }
 };
 
 }  // namespace vklb

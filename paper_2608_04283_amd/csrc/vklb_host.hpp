@@ -128,10 +128,47 @@ inline int default_band(const vklb_grid* g, int width) {
 }
 // Largest band: the MHD march of the delta bases collides a band's halo cells
 // into LDS for up to 64 rows; the others take any height.
-inline int max_band(int kind, int dim, int basis) { return kind == VKLB_MHD_GLM && dim == 2 && basis >= 1 ? 64 : 4096; }
+constexpr int kMaxBand = 4096;
+inline int max_band(int kind, int dim, int basis) {
+  return kind == VKLB_MHD_GLM && dim == 2 && basis >= 1 ? 64 : kMaxBand;
+}
 // Rows of halo columns per batch (1..32): measured fastest on MI355X with the
 // default bands, one batch per band (MHD 8 rows; the others 32, 3% over 2).
 inline int default_halo(int kind) { return kind == VKLB_MHD_GLM ? 8 : 32; }
+
+// Solves with omega = 1 keep U alone (vklb_omega1.hpp): the collision then
+// returns the equilibrium of U, so the populations between two steps carry
+// nothing that U does not.
+inline bool keeps_u(int dim, double omega) { return dim == 2 && omega == 1.0; }
+
+// Workgroups of a 2D step of such a solve (a wavefront per 64 columns and
+// `band` rows), and its default band.
+inline long long ustep_waves(const vklb_grid* g, int band) {
+  return ((g->n[0] + 63) / 64) * ((g->n[1] + band - 1) / band);
+}
+inline int ustep_grid_of(const vklb_grid* g, int band) {
+  return int((ustep_waves(g, band) + kUWaves - 1) / kUWaves);
+}
+// Rows per band of such a step: as few as let every wavefront be resident at
+// once, so that a grid is one round of wavefronts whatever its sides are; a
+// shorter band collides more edge rows (two half rows and the halo columns a
+// band), a taller one leaves SIMDs short of wavefronts. Resident wavefronts
+// per SIMD follow from the march's registers: four are enough in FP32 (SW,
+// Euler; more would fit), two in FP64 and for MHD, one for FP64 MHD. At most
+// 16 rows (MHD 32): large grids then take several rounds, whose wavefronts
+// are out of step. Measured on MI355X (FP32, us per step by rows): Euler
+// 2048^2 43.5 (8), 42.8 (16), 47.9 (32); 1024^2 18.3 (2), 14.9 (4), 15.3 (8);
+// 512^2 8.7 (1), 7.6 (2), 8.6 (4); 4096^2 150 (16), 171 (32), 166 (64); shallow
+// water 500 x 333 6.4 (1), 6.4 (2), 7.3 (4); MHD 1024^2 70.7 (4), 62.3 (8),
+// 87.7 (16); 2048^2 217 (16), 211 (32), 320 (64); FP64 Euler 1024^2 38.8 (4),
+// 34.3 (8), 38.8 (16); FP64 MHD 512^2 75.1 (2), 60.5 (4), 96.1 (8).
+inline int default_uband(int kind, vklb_precision prec, const vklb_grid* g) {
+  const bool mhd = kind == VKLB_MHD_GLM;
+  const long long waves = 1024ll * (prec == VKLB_FP32 ? (mhd ? 2 : 4) : (mhd ? 1 : 2));
+  const long long rows = ((g->n[0] + 63) / 64 * g->n[1] + waves - 1) / waves;
+  const long long most = mhd ? 32 : 16;
+  return int(rows < 2 ? 2 : (rows > most ? most : rows));
+}
 
 inline int step_grid_of(const vklb_grid* g, int width, int band) {
   if (g->dim == 1) return int((g->n[0] + width - 3) / (width - 2));
@@ -260,6 +297,17 @@ inline SolveDesc make_desc(char* base, const Layout& L, const vklb_system* sys, 
   d.nfull = grid->dim == 2 && band > 0 ? int(d.ny / band) : 0;
   d.halo = halo;
   d.nblocks = step_grid_of(grid, width, band);
+  if (keeps_u(grid->dim, omega)) {
+    // both U buffers in the first population buffer; the second one is the
+    // room for a checkpoint's populations, whose rows are in grid order
+    const size_t planes = size_t(L.slots > L.Q ? 2 : 1) * L.p;
+    d.ustate = 1;
+    d.us = (grid->n[0] + 63) / 64 * 64;
+    d.pop = d.fb;
+    d.fb = base + L.fa_off + planes * size_t(d.us) * d.ny * L.elem;
+    d.nfull = 0;
+    if (grid->dim == 2) d.nblocks = ustep_grid_of(grid, band);
+  }
   d.nred = d.nblocks;
   return d;
 }

@@ -51,7 +51,7 @@ struct DevState {
   double T;                       // end time (inf: none)
   long long max_steps;
   unsigned long long err_word;    // min over detections of (step << 32 | cell); ~0 if none
-  double pad[3];
+  double last[3];                 // xi, Lambda, c_h of the last step taken (or of the initialization)
 };
 
 // Everything a kernel needs to know about one solve (passed by value).
@@ -82,6 +82,9 @@ struct SolveDesc {
   int npar;              // parity of the step index at launches of parity 0
   int nred;              // partials a step launch reduces at entry: nblocks, or 1 when
                          // each launch's partials are folded into entry 0 after it
+  int ustate;            // 1: omega = 1, fa and fb hold U alone (vklb_omega1.hpp)
+  long long us;          // U buffers: values from one plane of a row to the next
+  void* pop;             // U solves: room for the populations of a checkpoint (may be null)
 };
 
 // Row of the population buffers that holds grid row r (2D). March step i of
@@ -314,6 +317,15 @@ __device__ inline Step begin_step(const SolveDesc& sd, double* red) {
 // pause) loads again from the buffer of n.
 __device__ inline int predicted_parity(const SolveDesc& sd) { return (sd.par ^ sd.npar) & 1; }
 
+// Speeds the populations of the coming state are built with: a U solve
+// rebuilds them from these (k_upopulate).
+__device__ inline void store_last(const SolveDesc& sd, const Step& S) {
+  gmem<DevState>* st = gl(sd.st);
+  st->last[0] = S.xi;
+  st->last[1] = S.lam;
+  st->last[2] = S.ch;
+}
+
 // End of a step: store this workgroup's maxima for the next launch; workgroup 0
 // advances (t, n) for it, or carries a finished state over unchanged.
 __device__ inline void end_step(const SolveDesc& sd, const Step& S, int tile, double lam, double cfm) {
@@ -329,6 +341,7 @@ __device__ inline void end_step(const SolveDesc& sd, const Step& S, int tile, do
       nx.done = 0;
       nx.pad = 0;
       store_scal(gl(sd.st), np, nx);
+      if (sd.ustate) store_last(sd, S);
     }
   }
 }

@@ -3,7 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
-#include "vklb_kernels.hpp"
+#include "vklb_omega1.hpp"
 
 namespace vklb {
 
@@ -21,6 +21,24 @@ struct Launchers {
   wg_fn run_wg = nullptr;        // 1D grids of up to wg_max_cells: many steps in one workgroup
   int wg_max_cells = 0;
   int block = 256;  // threads per step workgroup
+  // solves with omega = 1, which keep U alone (ustep null: not built for the dimension)
+  launch_fn ustep = nullptr;
+  launch_fn uinit = nullptr;
+  launch_fn umoments = nullptr;
+  launch_fn upopulate = nullptr;        // populations of the current step, after at least one step
+  launch_fn upopulate_first = nullptr;  // and before the first one
+  launch_fn uextract = nullptr;
+  batched_fn ubatched = nullptr;
+
+  // The launchers of a solve that keeps U, in the places of the others.
+  Launchers for_ustate() const {
+    Launchers L = *this;
+    L.step = ustep;
+    L.init_feq = uinit;
+    L.moments = umoments;
+    L.batched = ubatched;
+    return L;
+  }
 };
 
 // prec: 0 FP64, 1 FP32; basis: 0 populations, 1 delta, 2 compensated delta

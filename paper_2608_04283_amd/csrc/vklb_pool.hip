@@ -39,10 +39,10 @@ using namespace vklb;
 
 namespace {
 
-constexpr int kClasses = 8;   // (system kind) x (dimension)
+constexpr int kClasses = 16;  // (system kind) x (dimension) x (keeps U)
 constexpr int kMaxSlots = 4096;
 
-inline int class_of(int kind, int dim) { return kind * 2 + (dim - 1); }
+inline int class_of(int kind, int dim, bool ustate) { return (kind * 2 + (dim - 1)) * 2 + (ustate ? 1 : 0); }
 
 // First-fit allocator over [0, size) with coalescing of freed neighbours.
 class Arena {
@@ -159,7 +159,7 @@ struct vklb_pool {
   vklb_precision prec = VKLB_FP32;
   int basis[3] = {0, 0, 0};  // stored basis per dimension (index 1, 2)
   hipStream_t stream = nullptr;
-  hipStream_t cls_stream[kClasses] = {};   // default priority, non-blocking
+  hipStream_t cls_stream[kClasses] = {};   // default priority, non-blocking; made with a class's first round
   hipEvent_t ev_main = nullptr;
   hipEvent_t ev_cls[kClasses] = {};
   int device = 0;
@@ -206,21 +206,23 @@ vklb_status pfail(vklb_pool* p, vklb_status st, const std::string& m) {
 // Half-octave size class of a 2D grid side: round(2 log2 n).
 int size_class(long long n) { return int(lround(2.0 * log2(double(n > 0 ? n : 1)))); }
 
-// Tuned 2D shapes, kept for the process: (device, precision, kind, size
-// class) -> (band, halo).
+// Tuned 2D shapes, kept for the process: (device, precision, kind, keeps U,
+// size class) -> (band, halo).
 std::mutex g_tiles_mu;
-std::map<std::array<int, 4>, std::pair<int, int>> g_tiles;
+std::map<std::array<int, 5>, std::pair<int, int>> g_tiles;
 
 // Band and halo heights for a 2D solve of this kind and side: the tuned entry
 // of its size class, else the nearest tuned class of the kind, else (no tuned
 // entry) *band and *halo as given.
-void pick_shape(const vklb_pool* p, int kind, long long n, int* band, int* halo) {
+void pick_shape(const vklb_pool* p, int kind, bool ustate, long long n, int* band, int* halo) {
   const int want = size_class(n);
   int bestd = 1 << 30;
   std::lock_guard<std::mutex> lk(g_tiles_mu);
   for (const auto& kv : g_tiles) {
-    if (kv.first[0] != p->device || kv.first[1] != int(p->prec) || kv.first[2] != kind) continue;
-    const int d = abs(kv.first[3] - want);
+    if (kv.first[0] != p->device || kv.first[1] != int(p->prec) || kv.first[2] != kind ||
+        kv.first[3] != int(ustate))
+      continue;
+    const int d = abs(kv.first[4] - want);
     if (d < bestd) {
       bestd = d;
       *band = kv.second.first;
@@ -255,6 +257,7 @@ vklb_status admit(vklb_pool* p) {
     const int width = r->grid.dim == 1 ? 256 : 128;  // the batched kernels' tile widths
     r->sd = make_desc(p->base + off, r->L, &r->sys, &r->grid, &r->speed, r->omega, r->bc, &r->eq, width, r->band,
                       r->halo);
+    r->sd.pop = nullptr;  // the pool takes no checkpoints
     r->sd.npar = int(p->round & 1);  // step 0 runs at the parity of the next round
     if (r->sd.nblocks > kFoldAbove) r->sd.nred = 1;  // as a single solve: partials folded after each round
     // initialization into the parity of the next round
@@ -354,16 +357,14 @@ vklb_status vklb_pool_create(size_t hbm_budget, vklb_precision prec, void* hip_s
   if ((e = hipMalloc(&p->d_status, sizeof(SlotStatus) * kMaxSlots)) != hipSuccess) return cleanup(e);
   if ((e = hipHostMalloc(&p->h_status, sizeof(SlotStatus) * kMaxSlots, hipHostMallocDefault)) != hipSuccess)
     return cleanup(e);
-  for (int c = 0; c < kClasses; ++c) {
-    if ((e = hipStreamCreateWithFlags(&p->cls_stream[c], hipStreamNonBlocking)) != hipSuccess) return cleanup(e);
-    if ((e = hipEventCreateWithFlags(&p->ev_cls[c], hipEventDisableTiming)) != hipSuccess) return cleanup(e);
-  }
   if ((e = hipEventCreateWithFlags(&p->ev_main, hipEventDisableTiming)) != hipSuccess) return cleanup(e);
   p->arena.reset(p->budget);
   for (int kind = 0; kind < 4; ++kind)
-    for (int dim = 1; dim <= 2; ++dim)
-      p->cls_launch[class_of(kind, dim)] =
-          pick_launchers(kind, dim, prec == VKLB_FP32 ? 1 : 0, p->basis[dim], dim == 1 ? 256 : 128);
+    for (int dim = 1; dim <= 2; ++dim) {
+      const Launchers K = pick_launchers(kind, dim, prec == VKLB_FP32 ? 1 : 0, p->basis[dim], dim == 1 ? 256 : 128);
+      p->cls_launch[class_of(kind, dim, false)] = K;
+      p->cls_launch[class_of(kind, dim, true)] = K.for_ustate();
+    }
   p->stats.arena_bytes = p->budget;
   *out = p;
   return VKLB_OK;
@@ -397,11 +398,14 @@ vklb_status vklb_pool_submit(vklb_pool* p, const vklb_request* rq, uint64_t* tic
   const long long cells = r->grid.n[0] * (r->grid.dim == 2 ? r->grid.n[1] : 1);
   r->U0.assign(rq->U0, rq->U0 + size_t(r->L.p) * cells);
   r->U_out = rq->U_out;
-  r->cls = class_of(r->sys.kind, r->grid.dim);
-  r->band = r->grid.dim == 2 ? default_band(&r->grid, 128) : 32;  // the batched 2D strips are 128 columns
+  const bool ust = keeps_u(r->grid.dim, r->omega);
+  r->cls = class_of(r->sys.kind, r->grid.dim, ust);
+  r->band = 32;
+  if (r->grid.dim == 2)  // the batched 2D strips are 128 columns, a U solve's 64
+    r->band = ust ? default_uband(r->sys.kind, p->prec, &r->grid) : default_band(&r->grid, 128);
   r->halo = default_halo(r->sys.kind);
-  if (r->grid.dim == 2) pick_shape(p, r->sys.kind, r->grid.n[0], &r->band, &r->halo);
-  r->band = std::min(r->band, max_band(r->sys.kind, r->grid.dim, p->basis[r->grid.dim]));
+  if (r->grid.dim == 2) pick_shape(p, r->sys.kind, ust, r->grid.n[0], &r->band, &r->halo);
+  r->band = std::min(r->band, ust ? kMaxBand : max_band(r->sys.kind, r->grid.dim, p->basis[r->grid.dim]));
   p->queue.push_back(r);
   p->stats.submitted++;
   if (ticket) *ticket = r->ticket;
@@ -428,6 +432,8 @@ vklb_status vklb_pool_run(vklb_pool* p, int rounds) {
     }
     p->changed[c] = false;
     if (!p->nwork[c]) continue;
+    if (!p->cls_stream[c]) PCHK(p, hipStreamCreateWithFlags(&p->cls_stream[c], hipStreamNonBlocking));
+    if (!p->ev_cls[c]) PCHK(p, hipEventCreateWithFlags(&p->ev_cls[c], hipEventDisableTiming));
     hipStream_t cs = p->cls_stream[c];
     PCHK(p, hipStreamWaitEvent(cs, p->ev_main, 0));
     if (p->gexec[c] && (p->graph_rounds[c] != rounds || p->graph_par[c] != par0)) drop_class_graph(p, c);
@@ -571,7 +577,8 @@ vklb_status vklb_pool_autotune(vklb_pool* p, const vklb_request* samples, int n,
     if (st != VKLB_OK) return pfail(p, st, std::string("vklb_pool_autotune: ") + vklb_last_error(nullptr));
     {
       std::lock_guard<std::mutex> lk(g_tiles_mu);
-      g_tiles[{p->device, int(p->prec), int(r.sys.kind), size_class(r.grid.n[0])}] = {band, halo};
+      g_tiles[{p->device, int(p->prec), int(r.sys.kind), int(keeps_u(2, r.omega)), size_class(r.grid.n[0])}] = {band,
+                                                                                                              halo};
     }
     if (out && n_out && written < *n_out) {
       vklb_pool_tile& t = out[written++];

@@ -191,6 +191,7 @@ struct vklb_solver {
   int device = 0;
   int basis = 0;
   long long launches = 0;   // step launches since init (selects the parity)
+  long long pop_n = -1;     // U solves: step whose populations sd.pop holds (-1: none)
   int wg_cells = 0;         // > 0: 1D steps run in one workgroup, this many cells per lane
   int wg_lanes = 0;         // and this many lanes
 };
@@ -408,9 +409,12 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
     width = default_width(grid->dim, grid->n[0]);
   pl->width = width;
   pl->K = pick_launchers(sys->kind, grid->dim, prec == VKLB_FP32 ? 1 : 0, pl->basis, width);
+  const bool ust = keeps_u(grid->dim, omega);
+  if (ust) pl->K = pl->K.for_ustate();
   int band = o.band_rows;
-  if (band < 1) band = default_band(grid, width);
-  if (band > max_band(sys->kind, grid->dim, pl->basis)) band = max_band(sys->kind, grid->dim, pl->basis);
+  if (band < 1) band = ust ? default_uband(sys->kind, prec, grid) : default_band(grid, width);
+  const int top = ust ? kMaxBand : max_band(sys->kind, grid->dim, pl->basis);
+  if (band > top) band = top;
   pl->band = band;
   int halo = o.halo_rows;
   if (halo < 1 || halo > 32) halo = default_halo(sys->kind);
@@ -419,7 +423,8 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
   // nblocks^2 loads per step (10^12 at a million workgroups), so above the
   // threshold each launch's partials are folded into one entry instead.
   const int fold = o.fold_partials == 0 ? kFoldAbove : o.fold_partials;
-  pl->nred_one = fold > 0 && step_grid_of(&pl->grid, width, band) > fold;
+  pl->nred_one = fold > 0 && (ust && grid->dim == 2 ? ustep_grid_of(&pl->grid, band)
+                                                    : step_grid_of(&pl->grid, width, band)) > fold;
   // small 1D grids: whole step sequences in one workgroup (bitwise the same)
   pl->wg_cells = pl->wg_lanes = 0;
   if (grid->dim == 1 && o.small_grid >= 0 && pl->K.run_wg && grid->n[0] <= pl->K.wg_max_cells) {
@@ -549,6 +554,7 @@ static vklb_status init_from(vklb_solver* s, const double* U0, hipMemcpyKind kin
   st = fold_partials(s, s->stream, 0);
   if (st != VKLB_OK) return st;
   HIPCHK(s, s->K.init_feq(d, grid_for_cells(cells), s->stream));
+  s->pop_n = s->sd.ustate && s->basis == 0 ? 0 : -1;  // the sum form keeps the populations it starts from
   s->inited = true;
   return VKLB_OK;
 }
@@ -703,6 +709,16 @@ vklb_status vklb_get_state(vklb_solver* s, void* host, double* t, int64_t* steps
   if (st != VKLB_OK) return st;
   const size_t pop = vklb_state_bytes(s) - sizeof(CkptTrailer);
   const char* src = (v.S.n & 1) ? static_cast<const char*>(s->sd.fb) : static_cast<const char*>(s->sd.fa);
+  if (s->sd.ustate) {
+    src = static_cast<const char*>(s->sd.pop);
+    if (s->pop_n != v.S.n) {
+      SolveDesc d = s->sd;
+      d.par = int(s->launches & 1);
+      const int grid = grid_for_cells((long long)d.nx * d.ny);
+      HIPCHK(s, v.S.n == 0 ? s->K.upopulate_first(d, grid, s->stream) : s->K.upopulate(d, grid, s->stream));
+      s->pop_n = v.S.n;
+    }
+  }
   HIPCHK(s, hipMemcpyAsync(host, src, pop, hipMemcpyDeviceToHost, s->stream));
   HIPCHK(s, hipStreamSynchronize(s->stream));
   if (s->sd.nfull > 1) {  // rows to grid order
@@ -732,6 +748,7 @@ vklb_status vklb_set_state(vklb_solver* s, const void* host) {
       tr.basis != me.basis || tr.nx != me.nx || tr.ny != me.ny || tr.n < 0)
     return fail(s, VKLB_ERR_ARG, "checkpoint does not belong to a solver of this shape");
   char* dst = (tr.n & 1) ? static_cast<char*>(s->sd.fb) : static_cast<char*>(s->sd.fa);
+  if (s->sd.ustate) dst = static_cast<char*>(s->sd.pop);
   if (s->sd.nfull > 1) {  // rows to the device's order
     std::vector<char> dev(pop, 0);
     reorder_rows(static_cast<const char*>(host), dev.data(), s->sd, s->L, s->sys.kind == VKLB_MHD_GLM, false);
@@ -747,6 +764,13 @@ vklb_status vklb_set_state(vklb_solver* s, const void* host) {
   part[0] = tr.lam7;
   part[s->sd.nblocks] = tr.cfm;
   HIPCHK(s, hipMemcpyAsync(s->sd.part, part.data(), part.size() * 8, hipMemcpyHostToDevice, s->stream));
+  s->pop_n = -1;
+  if (s->sd.ustate) {
+    SolveDesc d = s->sd;
+    d.par = 0;
+    HIPCHK(s, s->K.uextract(d, grid_for_cells((long long)d.nx * d.ny), s->stream));
+    s->pop_n = tr.n;
+  }
   HIPCHK(s, hipStreamSynchronize(s->stream));
   s->inited = true;
   return VKLB_OK;
@@ -771,12 +795,14 @@ static vklb_status tune_impl(const vklb_system* sys, vklb_lattice lat, const vkl
   else memset(&b0, 0, sizeof b0);
   // candidate tile shapes
   std::vector<vklb_options> cand;
+  // a solve that keeps U has one strip width and one halo batch
+  const bool ust = keeps_u(grid->dim, omega);
   if (pool_2d) {
     const long long ny = grid->n[1];
     for (int band : {4, 8, 16, 32, 64}) {
       if (band > 4 && band / 2 >= ny) continue;
       for (int halo : {2, 8, 16, 32}) {
-        if (halo > band) continue;
+        if (halo > band || (ust && halo > 2)) continue;
         vklb_options o = b0;
         o.strip_width = 128;
         o.band_rows = band;
@@ -802,15 +828,17 @@ static vklb_status tune_impl(const vklb_system* sys, vklb_lattice lat, const vkl
   } else {
     const long long nx = grid->n[0], ny = grid->n[1];
     for (int w : {64, 128, 256}) {
+      if (ust && w > 64) continue;
       if (w > 64 && (nx + w - 1) / w * w - nx >= w / 2) continue;  // mostly idle lanes
       // the default rule's band too, where it is taller than these (large grids)
       std::vector<int> bands = {4, 8, 16, 32, 64};
-      const int rule = std::min(default_band(grid, w), max_band(sys->kind, 2, resolve_basis(b0.basis, prec, 2)));
+      const int rule = ust ? default_uband(sys->kind, prec, grid)
+                           : std::min(default_band(grid, w), max_band(sys->kind, 2, resolve_basis(b0.basis, prec, 2)));
       if (rule > 64) bands.push_back(rule);
       for (int band : bands) {
         if (band > 4 && band / 2 >= ny) continue;
         for (int halo : {2, 8, 16, 32}) {
-          if (halo > band) continue;
+          if (halo > band || (ust && halo > 2)) continue;
           vklb_options o = b0;
           o.strip_width = w;
           o.band_rows = band;
@@ -959,6 +987,7 @@ vklb_status vklb_run_static(const vklb_system* sys, vklb_lattice lat, const vklb
   if (st != VKLB_OK) return st;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
   SolveDesc sd = pl.bind(ws);
+  sd.pop = nullptr;  // no checkpoint can be asked for
   const long long cells = (long long)sd.nx * sd.ny;
   // vklb_init: scalars, xi^0 / c_h^0 from U0, f = f^eq(U0); U0 is read in
   // place, so the staging area is not used.

@@ -76,9 +76,10 @@ def tune_shapes(precision="fp32", steps=20, seed=11, sizes=TUNE_SIZES):
 
 
 def _alg_bytes(prob, precision):
-    """Algorithmic bytes of one cell-step: every population read once and
-    written once, 2 Q p s."""
-    return 2 * prob.Q * prob.p * (4 if precision == "fp32" else 8)
+    """Algorithmic bytes of one cell-step: the stored state read once and
+    written once (2D with omega = 1: U, 2 p s; else every population, 2 Q p s)."""
+    slots = 1 if prob.dim == 2 and prob.omega == 1.0 else prob.Q
+    return 2 * slots * prob.p * (4 if precision == "fp32" else 8)
 
 
 def run_batched(requests, budget_bytes, precision="fp32", chunk_rounds=64, realtime=True, keep_results=False,
