@@ -110,6 +110,48 @@ __host__ __device__ inline S beta_w(S lam, S half_k_over_L, int kinf) {
   return S(0.5) * wtanh(lam * half_k_over_L);
 }
 
+// beta of N speeds of one direction, none larger than lmax in magnitude. With
+// the sigmoid normalized by the largest |lambda| and k <= 2 (Sec. 3.1, k = 2)
+// every argument z = k lambda / (2 Lambda) lies in [-1, 1], where tanh(z) / 2 is
+// an odd polynomial, z p(z^2): 9 vector operations a weight in FP32 (degree 7)
+// and 17 in FP64 (degree 15), with no transcendental one among them, against
+// 11 and about 85 of wtanh. The coefficients are the interpolant of
+// tanh(sqrt w) / (2 sqrt w) at Chebyshev nodes of [0, 1.0414]; relative error
+// 1.1e-7 and 2.2e-16 over |z| <= 1.02, rounding included (wtanh in FP32: 1.6e-6
+// relative for |z| > 0.01, 6.5e-8 absolute against 4.3e-8 here). Larger
+// arguments (k > 2, or a boundary state faster than the grid) take wtanh.
+template <class S, int N>
+__host__ __device__ inline void weights(const S (&lam)[N], S lmax, S hk, int kinf, S (&b)[N]) {
+  if (!kinf && lmax * hk <= S(1.02)) {
+    constexpr double c32[8] = {0.5, -0.16666631400585175, 0.06665942817926407, -0.02692667953670025,
+                               0.010705825872719288, -0.0039176070131361485, 0.0011097308015450835,
+                               -0.00016730035713408142};
+    constexpr double c64[16] = {0.5, -0.16666666666666183, 0.06666666666626553, -0.02698412697101095,
+                                0.010934744042573333, -0.004431615413343778, 0.001796047850046346,
+                                -0.0007278399231292868, 0.0002947479495034335, -0.00011889149097278873,
+                                4.718446560211916e-05, -1.7825235404940583e-05, 6.004817950962269e-06,
+                                -1.6264485337714894e-06, 3.023335014179045e-07, -2.7998503351044707e-08};
+    constexpr int n = sizeof(S) == 4 ? 7 : 15;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const S z = lam[j] * hk, w = z * z;
+      S p = S(sizeof(S) == 4 ? c32[7] : c64[15]);
+#pragma unroll
+      for (int i = n - 1; i >= 0; --i) p = p * w + S(sizeof(S) == 4 ? c32[i & 7] : c64[i]);
+      b[j] = p * z;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < N; ++j) b[j] = beta_w(lam[j], hk, kinf);
+  }
+}
+
+// k / (2 L): the weights' argument is lambda times this.
+template <class S>
+__host__ __device__ inline S half_k_over(const Phys& ph, S L) {
+  return L > S(0) ? qdiv(S(0.5 * ph.k), L) : S(0);
+}
+
 // Divided difference (beta(a) - beta(b)) / (a - b) from the weights ba, bb
 // already evaluated, with the derivative when the two speeds nearly coincide.
 template <class S>
@@ -149,10 +191,11 @@ struct Cell<K_LINEAR, DIM, S> {
   // F^(d) and D^(d); Lam normalizes the sigmoid (global max |lambda|), ch unused.
   __host__ __device__ static void split(int d, const S* U, const Phys& ph, S Lam, S, S* F, S* D) {
     S a = S(ph.adv[d]);
-    S L = ph.alpha_local ? fabs(a) : Lam;
-    S hk = L > S(0) ? qdiv(S(0.5 * ph.k), L) : S(0);
+    const S hk = half_k_over(ph, ph.alpha_local ? S(fabs(a)) : Lam);
+    S lam[1] = {a}, b[1];
+    weights(lam, S(fabs(a)), hk, ph.kinf, b);
     F[0] = a * U[0];
-    D[0] = beta_w(a, hk, ph.kinf) * a * U[0];
+    D[0] = b[0] * a * U[0];
   }
 };
 
@@ -201,9 +244,22 @@ struct Cell<K_SW, DIM, S> {
     const S lm = ud - c, lp = ud + c;
     const S L = ph.alpha_local ? fmax(fabs(lm), fabs(lp)) : Lam;
     const S hk = L > S(0) ? qdiv(S(0.5 * ph.k), L) : S(0);
+    // The weights' polynomial (weights) is not used here except in 2D FP64. In
+    // FP32 the range check costs what it saves on two weights (a 100-cell solve
+    // in one workgroup: 1.39 us a step with it, 1.33 without). The 1D FP64
+    // results stay bit for bit: the dam break amplifies a rounding up to 10^8
+    // times at its rarefaction head, so any other rounding shows in them.
+    S b[2];
+    if (DIM == 2 && sizeof(S) == 8) {
+      const S lam[2] = {lm, lp};
+      weights(lam, S(fmax(fabs(lm), fabs(lp))), hk, ph.kinf, b);
+    } else {
+      b[0] = beta_w(lm, hk, ph.kinf);
+      b[1] = beta_w(lp, hk, ph.kinf);
+    }
     // coefficients of the two acoustic waves: phi = h (2 u_d -+ c) / 4
-    const S wm = beta_w(lm, hk, ph.kinf) * h * (S(2) * ud - c) * S(0.25);
-    const S wp = beta_w(lp, hk, ph.kinf) * h * (S(2) * ud + c) * S(0.25);
+    const S wm = b[0] * h * (S(2) * ud - c) * S(0.25);
+    const S wp = b[1] * h * (S(2) * ud + c) * S(0.25);
     D[0] = wm + wp;
     for (int kk = 0; kk < DIM; ++kk) D[1 + kk] = qdiv(U[1 + kk], h) * (wm + wp);
     D[1 + d] = lm * wm + lp * wp;
@@ -244,14 +300,14 @@ struct Cell<K_EULER, DIM, S> {
   __host__ __device__ static S pressure(const S* U, S gamma) {
     S m2 = S(0);
     for (int kk = 0; kk < DIM; ++kk) m2 += U[1 + kk] * U[1 + kk];
-    return (gamma - S(1)) * (U[DIM + 1] - S(0.5) * qdiv(m2, U[0]));
+    return (gamma - S(1)) * (U[DIM + 1] - S(0.5) * m2 * qrcp(U[0]));
   }
   __host__ __device__ static void speeds(const S* U, const Phys& ph, S* lam, S* cfm) {
     const S gamma = S(ph.gamma);
-    const S rho = U[0];
-    const S c = qsqrt(qdiv(gamma * pressure(U, gamma), rho));
+    const S irho = qrcp(U[0]);
+    const S c = qsqrt(gamma * pressure(U, gamma) * irho);
     S m = S(0);
-    for (int d = 0; d < DIM; ++d) m = fmax(m, fabs(qdiv(U[1 + d], rho)) + c);
+    for (int d = 0; d < DIM; ++d) m = fmax(m, fabs(U[1 + d] * irho) + c);
     *lam = m;
     *cfm = S(0);
   }
@@ -275,19 +331,24 @@ struct Cell<K_EULER, DIM, S> {
     for (int kk = 0; kk < DIM; ++kk) F[1 + kk] = U[1 + kk] * ud;
     F[1 + d] += p;
     F[DIM + 1] = (E + p) * ud;
-    const S l1 = ud - c, l3 = ud + c;
-    const S L = ph.alpha_local ? fmax(fabs(l1), fabs(l3)) : Lam;
-    const S hk = L > S(0) ? qdiv(S(0.5 * ph.k), L) : S(0);
-    const S mu1 = beta_w(l1, hk, ph.kinf) * l1;
-    const S mu2 = beta_w(ud, hk, ph.kinf) * ud;
-    const S mu3 = beta_w(l3, hk, ph.kinf) * l3;
+    const S lam[3] = {ud - c, ud, ud + c};
+    const S lmax = fabs(ud) + c;
+    const S hk = half_k_over(ph, ph.alpha_local ? lmax : Lam);
+    S b[3];
+    if (sizeof(S) == 8 || DIM == 2) {
+      weights(lam, lmax, hk, ph.kinf, b);
+    } else {
+      for (int j = 0; j < 3; ++j) b[j] = beta_w(lam[j], hk, ph.kinf);
+    }
+    const S mu1 = b[0] * lam[0], mu3 = b[2] * lam[2];
     const S H = (E + p) * irho;
-    const S s = qdiv(rho, S(2) * gamma);
-    const S ent = S(2) * (gamma - S(1)) * mu2;
-    D[0] = s * (ent + mu1 + mu3);
-    for (int kk = 0; kk < DIM; ++kk) D[1 + kk] = s * (ent + mu1 + mu3) * vel[kk];
-    D[1 + d] += s * c * (mu3 - mu1);
-    D[DIM + 1] = s * (ent * S(0.5) * v2 + mu1 * (H - ud * c) + mu3 * (H + ud * c));
+    const S s = rho * qrcp(S(2) * gamma);
+    const S ent = S(2) * (gamma - S(1)) * (b[1] * ud);
+    const S sum = mu1 + mu3, dif = c * (mu3 - mu1);
+    D[0] = s * (ent + sum);
+    for (int kk = 0; kk < DIM; ++kk) D[1 + kk] = D[0] * vel[kk];
+    D[1 + d] += s * dif;
+    D[DIM + 1] = s * (ent * (S(0.5) * v2) + H * sum + ud * dif);
   }
 };
 
@@ -329,20 +390,20 @@ struct Cell<K_MHD, DIM, S> {
     const double Bn = Ug[5], By = Ug[6], Bz = Ug[7];
     const double uu = u * u + v * v + w * w;
     const double p = gm1 * (Ug[4] - 0.5 * rho * uu - 0.5 * (Bn * Bn + By * By + Bz * Bz));
-    double eg[9];
+    typename C::template Eig<double> eg;
     C::template eigenstructure<double>(rho, p, Bn, By, Bz, gamma, eg);
     typename C::Waves W;
     W.rho = rho;
     W.sr = sqrt(rho);
-    W.a2 = eg[0];
-    W.a = eg[1];
-    W.cf = eg[2];
-    W.cs = eg[3];
-    const double ca = eg[4];
-    W.af = eg[5];
-    W.as = eg[6];
-    W.by = eg[7];
-    W.bz = eg[8];
+    W.a2 = eg.a2;
+    W.a = eg.a;
+    W.cf = eg.cf;
+    W.cs = eg.cs;
+    const double ca = eg.ca;
+    W.af = eg.af;
+    W.as = eg.as;
+    W.by = eg.by;
+    W.bz = eg.bz;
     W.sgn = Bn >= 0.0 ? 1.0 : -1.0;
     const double lam[7] = {u - W.cf, u - ca, u - W.cs, u, u + W.cs, u + ca, u + W.cf};
     auto out_ = [right](double l) { return right ? l > 0.0 : l < 0.0; };
@@ -388,14 +449,14 @@ struct Cell<K_MHD, DIM, S> {
   __host__ __device__ static S pressure(const S* U, S gamma) {
     S m2 = U[1] * U[1] + U[2] * U[2] + U[3] * U[3];
     S B2 = U[5] * U[5] + U[6] * U[6] + U[7] * U[7];
-    return (gamma - S(1)) * (U[4] - S(0.5) * qdiv(m2, U[0]) - S(0.5) * B2);
+    return (gamma - S(1)) * (U[4] - S(0.5) * m2 * qrcp(U[0]) - S(0.5) * B2);
   }
   // fast speed along direction d
   __host__ __device__ static S fast(const S* U, S gamma, int d) {
-    const S rho = U[0];
-    const S a2 = qdiv(gamma * pressure(U, gamma), rho);
-    const S bn2 = qdiv(U[5 + d] * U[5 + d], rho);
-    const S bt2 = qdiv(U[5] * U[5] + U[6] * U[6] + U[7] * U[7], rho) - bn2;
+    const S irho = qrcp(U[0]);
+    const S a2 = gamma * pressure(U, gamma) * irho;
+    const S bn2 = U[5 + d] * U[5 + d] * irho;
+    const S bt2 = (U[5 + (d + 1) % 3] * U[5 + (d + 1) % 3] + U[5 + (d + 2) % 3] * U[5 + (d + 2) % 3]) * irho;
     const S disc = qsqrt(sq(a2 - bn2) + bt2 * (S(2) * a2 + S(2) * bn2 + bt2));
     return qsqrt(S(0.5) * (a2 + bn2 + bt2 + disc));
   }
@@ -404,7 +465,7 @@ struct Cell<K_MHD, DIM, S> {
     S m = S(0), cm = S(0);
     for (int d = 0; d < DIM; ++d) {
       const S cf = fast(U, gamma, d);
-      m = fmax(m, fabs(qdiv(U[1 + d], U[0])) + cf);
+      m = fmax(m, fabs(U[1 + d] * qrcp(U[0])) + cf);
       cm = fmax(cm, cf);
     }
     *lam = m;   // seven-wave max; the cleaning speed joins it globally
@@ -464,64 +525,58 @@ struct Cell<K_MHD, DIM, S> {
     y[6] = w.bz * bp + w.by * bq;
   }
 
-  // Directions near the triple point, where the fast and slow speeds nearly
-  // meet (c_f^2 - c_s^2 = disc small: transverse field -> 0 and a^2 -> b_n^2
-  // together): the FP32 split computes their eigenstructure in FP64. Near the
+  // Wave speeds and Roe-Balsara normalization of one direction, in precision
+  // R: the squared sound, normal and transverse Alfven speeds give
+  //   disc = c_f^2 - c_s^2, c_f^2 = (a^2 + b^2 + disc) / 2, c_s = a c_a / c_f,
+  //   alpha_f^2 and alpha_s^2 = (disc +- (a^2 - b^2)) / (2 disc), the smaller one
+  // from their product a^2 b_t^2 / disc^2, without cancellation. Returns
+  // whether the direction is near the triple point, where the fast and slow
+  // speeds nearly meet (disc small: transverse field -> 0 and a^2 -> b_n^2
+  // together). The FP32 split then takes this structure from FP64. Near the
   // other coincidences (transverse field -> 0 alone, where the fast or slow
   // speed meets the Alfven speed, or normal field -> 0) the FP32 closed form
-  // with the Roe-Balsara normalization stays at FP32 rounding of the FP64
-  // split at every distance, so those stay in FP32; near the triple point it
-  // loses up to ~1e-6 without FP64.
-  __host__ __device__ static bool near_degenerate(int d, const S* U, S gamma) {
-    const S rho = U[0];
-    const S a2 = qdiv(gamma * pressure(U, gamma), rho);
-    const S bn2 = qdiv(U[5 + d] * U[5 + d], rho);
-    const S bt2 = qdiv(U[5] * U[5] + U[6] * U[6] + U[7] * U[7], rho) - bn2;
-    const S tot = a2 + bn2 + bt2;
-    const S disc2 = sq(a2 - bn2) + bt2 * (S(2) * a2 + S(2) * bn2 + bt2);
-    return disc2 < S(1e-4) * tot * tot;
-  }
-
-  // Wave speeds and Roe-Balsara normalization of one direction, in precision R.
+  // stays at FP32 rounding of the FP64 split at every distance; near the
+  // triple point it loses up to ~1e-6 without FP64.
   template <class R>
-  __host__ __device__ static void eigenstructure(R rho, R p, R Bn, R By, R Bz, R gamma, R* out) {
+  struct Eig {
+    R a2, a, cf, cs, ca, af, as, by, bz, bt;  // bt = |B_t|
+  };
+  template <class R>
+  __host__ __device__ static bool eigenstructure(R rho, R p, R Bn, R By, R Bz, R gamma, Eig<R>& e) {
     const R irho = qrcp(rho);
     const R a2 = gamma * p * irho;
     const R bn2 = Bn * Bn * irho;
     const R bt2r = By * By + Bz * Bz;
     const R bt2 = bt2r * irho;
     const R b2 = bn2 + bt2;
-    const R disc = qsqrt(sq(a2 - bn2) + bt2 * (R(2) * a2 + R(2) * bn2 + bt2));
-    const R cf2 = R(0.5) * (a2 + b2 + disc);
-    const R cs2 = cf2 > R(0) ? qdiv(a2 * bn2, cf2) : R(0);
-    R af, as, by, bz;
+    const R disc2 = sq(a2 - bn2) + bt2 * (R(2) * a2 + R(2) * bn2 + bt2);
+    const R disc = qsqrt(disc2);
+    const R tot = a2 + b2;
+    const R cf2 = R(0.5) * (tot + disc);
+    e.a2 = a2;
+    e.a = qsqrt(a2);
+    e.cf = qsqrt(cf2);
+    e.ca = qsqrt(bn2);
+    e.cs = cf2 > R(0) ? qdiv(e.a * e.ca, e.cf) : R(0);
+    e.af = R(1);
+    e.as = R(0);
     if (disc > R(0)) {
       const R diff = a2 - b2;
-      const R nf = diff >= R(0) ? R(0.5) * (diff + disc) : qdiv(R(2) * a2 * bt2, disc - diff);
-      const R ns = diff <= R(0) ? R(0.5) * (disc - diff) : qdiv(R(2) * a2 * bt2, disc + diff);
-      af = qsqrt(fmin(R(1), fmax(R(0), qdiv(nf, disc))));
-      as = qsqrt(fmin(R(1), fmax(R(0), qdiv(ns, disc))));
-    } else {
-      af = R(1);
-      as = R(0);
+      const R big = R(0.5) * (fabs(diff) + disc);
+      const R id = qrcp(disc);
+      const R nb = qsqrt(big * id), ns = qsqrt(qdiv(a2 * bt2, big) * id);
+      e.af = fmin(R(1), diff >= R(0) ? nb : ns);
+      e.as = fmin(R(1), diff >= R(0) ? ns : nb);
     }
+    e.by = e.bz = R(0.70710678118654752440);
+    e.bt = R(0);
     if (bt2r > R(0)) {
-      const R ibt = qrcp(qsqrt(bt2r));
-      by = By * ibt;
-      bz = Bz * ibt;
-    } else {
-      by = R(0.70710678118654752440);
-      bz = R(0.70710678118654752440);
+      e.bt = qsqrt(bt2r);
+      const R ibt = qrcp(e.bt);
+      e.by = By * ibt;
+      e.bz = Bz * ibt;
     }
-    out[0] = a2;
-    out[1] = qsqrt(a2);
-    out[2] = qsqrt(cf2);
-    out[3] = qsqrt(cs2);
-    out[4] = qsqrt(bn2);
-    out[5] = af;
-    out[6] = as;
-    out[7] = by;
-    out[8] = bz;
+    return disc2 < R(1e-4) * tot * tot;
   }
 
   __host__ __device__ static void split(int d, const S* Ug, const Phys& ph, S Lam, S ch, S* Fg, S* Dg) {
@@ -551,70 +606,86 @@ struct Cell<K_MHD, DIM, S> {
     F[6] = u * By - Bn * v;
     F[7] = u * Bz - Bn * w;
     F[8] = ch * ch * Bn;
-    // wave speeds and Roe-Balsara normalization; in FP32 the directions whose
-    // speeds nearly coincide get this eigenstructure in FP64
-    Waves W;
-    W.rho = rho;
-    W.sr = qsqrt(rho);
-    S eg[9];
-    if (sizeof(S) == 4 && near_degenerate(d, Ug, gamma)) {
-      double e64[9];
-      eigenstructure<double>(double(rho), double(p), double(Bn), double(By), double(Bz), double(gamma), e64);
-      for (int i = 0; i < 9; ++i) eg[i] = S(e64[i]);
+    // wave speeds and Roe-Balsara normalization; in FP32 the directions near
+    // the triple point get this eigenstructure in FP64
+    Eig<S> e;
+    if (eigenstructure<S>(rho, p, Bn, By, Bz, gamma, e) && sizeof(S) == 4) {
+      Eig<double> f;
+      eigenstructure<double>(double(rho), double(p), double(Bn), double(By), double(Bz), double(gamma), f);
+      e = {S(f.a2), S(f.a), S(f.cf), S(f.cs), S(f.ca), S(f.af), S(f.as), S(f.by), S(f.bz), S(f.bt)};
+    }
+    const S sgn = Bn >= S(0) ? S(1) : S(-1);
+    // speeds (f-, a-, s-, e, s+, a+, f+) and their weights
+    const S lam[7] = {u - e.cf, u - e.ca, u - e.cs, u, u + e.cs, u + e.ca, u + e.cf};
+    const S lmax = fabs(u) + e.cf;
+    S hk = half_k_over(ph, Lam);
+    S bcp = beta_w(ch, hk, ph.kinf);
+    if (ph.alpha_local) {
+      hk = half_k_over(ph, S(fmax(lmax, ch)));
+      bcp = beta_w(ch, hk, ph.kinf);
+    }
+    S b[7];
+    weights(lam, lmax, hk, ph.kinf, b);
+    // Coefficients in the seven primitive eigenvectors of the flux (F) and of
+    // the B_n column of the Jacobian (C). Both are taken in the frame of the
+    // transverse field, t = (by, bz): their transverse momentum parts lie along
+    // it (xvq = 0) and most of the flux cancels in its primitive image,
+    //   x_F = (rho u, (p_t - B_n^2) / rho, -B_n B_t / rho, 0,
+    //          u p + (gamma - 1) (u (B_n^2 - B_t^2) / 2 + B_n B_t v_t), u B_t - B_n v_t, -B_n v_q),
+    //   x_C = (0, -gamma B_n / rho, -B_t / rho, 0, (gamma - 1) B_t v_t, -v_t, -v_q).
+    const S vp = e.by * v + e.bz * w, vq = e.by * w - e.bz * v;
+    const S ia = qrcp(e.a), ia2 = ia * ia, sr = qsqrt(rho), isr = sr * irho;
+    const S bt = e.bt, ia2r = ia2 * irho, ias = ia * isr;
+    const S afcf = e.af * e.cf, ascs = e.as * e.cs;
+    struct Coef {
+      S fm, fp, sm, sp, a, e;  // f-, f+, s-, s+, a- = a+, entropy
+    };
+    auto expand = [&](S x0, S x1, S xvp, S x4, S xbp, S xbq) {
+      const S X = x4 * ia2r, Y = xbp * ias, Z2 = sgn * xvp;
+      const S Fp = e.af * X + e.as * Y, Sp = e.as * X - e.af * Y;
+      const S Fm = (afcf * x1 - ascs * Z2) * ia2, Sm = (ascs * x1 + afcf * Z2) * ia2;
+      return Coef{S(0.5) * (Fp - Fm), S(0.5) * (Fp + Fm), S(0.5) * (Sp - Sm), S(0.5) * (Sp + Sm),
+                  S(0.5) * (xbq * isr), x0 - x4 * ia2};
+    };
+    const S x4c = gm1 * (bt * vp), x4f = u * p + gm1 * (S(0.5) * u * (Bn * Bn - bt * bt)) + Bn * x4c;
+    const Coef f = expand(F[0], (pt - Bn * Bn) * irho, -Bn * bt * irho, x4f, u * bt - Bn * vp, -Bn * vq);
+    const Coef c = expand(S(0), -gamma * Bn * irho, -bt * irho, x4c, -vp, -vq);
+    // s_j: divided differences of the weights between lambda_j and +-c_h, times
+    // the cleaning pair's coefficients (psi +- c_h B_n) / 2. Over the common
+    // denominator that is one reciprocal a wave; it is used where the speeds
+    // are well apart from c_h (c_h is six times the largest fast speed).
+    S s[7];
+    if (lmax <= S(0.5) * ch) {
+      const S c2 = ch * ch, c2B = c2 * Bn, bc = bcp * ch;
+#pragma unroll
+      for (int j = 0; j < 7; ++j)
+        s[j] = (b[j] * (lam[j] * psi + c2B) - bc * (lam[j] * Bn + psi)) * qrcp(lam[j] * lam[j] - c2);
     } else {
-      eigenstructure<S>(rho, p, Bn, By, Bz, gamma, eg);
+      const S qp = S(0.5) * (psi + ch * Bn), qm = S(0.5) * (psi - ch * Bn);
+      const S bcm = beta_w(-ch, hk, ph.kinf);
+#pragma unroll
+      for (int j = 0; j < 7; ++j)
+        s[j] = beta_dd(lam[j], b[j], ch, bcp, hk, ph.kinf) * qp + beta_dd(lam[j], b[j], -ch, bcm, hk, ph.kinf) * qm;
     }
-    W.a2 = eg[0];
-    W.a = eg[1];
-    W.cf = eg[2];
-    W.cs = eg[3];
-    const S ca = eg[4];
-    W.af = eg[5];
-    W.as = eg[6];
-    W.by = eg[7];
-    W.bz = eg[8];
-    W.sgn = Bn >= S(0) ? S(1) : S(-1);
-    // speeds (f-, a-, s-, e, s+, a+, f+)
-    S lam[7] = {u - W.cf, u - ca, u - W.cs, u, u + W.cs, u + ca, u + W.cf};
-    const S L = ph.alpha_local ? fmax(fmax(fabs(lam[0]), fabs(lam[6])), ch) : Lam;
-    const S hk = L > S(0) ? qdiv(S(0.5 * ph.k), L) : S(0);
-    // primitive images of the seven-wave flux and of the B_n column of the Jacobian
-    S xF[7], xC[7];
-    xF[0] = F[0];
-    xF[1] = (F[1] - u * F[0]) * irho;
-    xF[2] = (F[2] - v * F[0]) * irho;
-    xF[3] = (F[3] - w * F[0]) * irho;
-    xF[4] = gm1 * (F[4] + S(0.5) * uu * F[0] - (u * F[1] + v * F[2] + w * F[3]) - By * F[6] - Bz * F[7]);
-    xF[5] = F[6];
-    xF[6] = F[7];
-    xC[0] = S(0);
-    xC[1] = -gamma * Bn * irho;
-    xC[2] = -By * irho;
-    xC[3] = -Bz * irho;
-    xC[4] = gm1 * (v * By + w * Bz);
-    xC[5] = -v;
-    xC[6] = -w;
-    S cF[7], cC[7], cD[7];
-    project(W, xF, cF);
-    project(W, xC, cC);
-    const S qp = S(0.5) * (psi + ch * Bn), qm = S(0.5) * (psi - ch * Bn);
-    const S bcp = beta_w(ch, hk, ph.kinf), bcm = beta_w(-ch, hk, ph.kinf);
-    for (int j = 0; j < 7; ++j) {
-      const S bj = beta_w(lam[j], hk, ph.kinf);
-      const S sj = beta_dd(lam[j], bj, ch, bcp, hk, ph.kinf) * qp + beta_dd(lam[j], bj, -ch, bcm, hk, ph.kinf) * qm;
-      cD[j] = bj * cF[j] + sj * cC[j];
-    }
-    S y[7];
-    combine(W, cD, y);
+    // the weighted sum of the eigenvectors: a primitive vector y in the same frame
+    const S d0 = b[0] * f.fm + s[0] * c.fm, d6 = b[6] * f.fp + s[6] * c.fp;
+    const S d2 = b[2] * f.sm + s[2] * c.sm, d4 = b[4] * f.sp + s[4] * c.sp;
+    const S Fp = d6 + d0, Fm = d6 - d0, Sp = d4 + d2, Sm = d4 - d2;
+    const S Ap = (b[5] + b[1]) * f.a + (s[5] + s[1]) * c.a, Am = (b[5] - b[1]) * f.a + (s[5] - s[1]) * c.a;
+    const S rpf = rho * (e.af * Fp + e.as * Sp);
+    const S y0 = b[3] * f.e + s[3] * c.e + rpf;
+    const S y1 = afcf * Fm + ascs * Sm;
+    const S yvp = sgn * (afcf * Sm - ascs * Fm), yvq = -sgn * Am;
+    const S ybp = e.a * sr * (e.as * Fp - e.af * Sp), ybq = sr * Ap;
     // back to conserved variables (B_n fixed in the seven-wave block)
     S D[9];
-    D[0] = y[0];
-    D[1] = u * y[0] + rho * y[1];
-    D[2] = v * y[0] + rho * y[2];
-    D[3] = w * y[0] + rho * y[3];
-    D[4] = qdiv(y[4], gm1) + S(0.5) * uu * y[0] + rho * (u * y[1] + v * y[2] + w * y[3]) + By * y[5] + Bz * y[6];
-    D[6] = y[5];
-    D[7] = y[6];
+    D[0] = y0;
+    D[1] = u * y0 + rho * y1;
+    D[2] = v * y0 + rho * (e.by * yvp - e.bz * yvq);
+    D[3] = w * y0 + rho * (e.bz * yvp + e.by * yvq);
+    D[4] = qdiv(e.a2 * rpf, gm1) + S(0.5) * uu * y0 + rho * (u * y1 + vp * yvp + vq * yvq) + bt * ybp;
+    D[6] = e.by * ybp - e.bz * ybq;
+    D[7] = e.bz * ybp + e.by * ybq;
     const S eta = bcp * ch;
     D[5] = eta * Bn;
     D[8] = eta * psi;
