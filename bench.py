@@ -17,7 +17,7 @@ request stream under "serving".
 
 Prints one JSON line: value = cells x time steps / second (Mcell-steps/s) of
 the timed solves; roofline = algorithmic bytes of the step kernel (the stored
-state read once and written once: U, 2 p s bytes per cell-step, in 2D solves
+state read once and written once: U, 2 p s bytes per cell-step, in solves
 with omega = 1; every population, 2 Q p s, in the others; times the cells and
 steps of a launch) over its average launch duration, measured with HIP events
 on the solver's stream; cpu_baseline = the FP64 oracle on a
@@ -65,11 +65,16 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
+def keeps_u(P, prec):
+    """The library's rule for the solves that store U alone."""
+    return P.omega == 1.0 and not (P.system == "sw" and P.dim == 1 and prec == "fp64")
+
+
 def alg_bytes_per_cell_step(P, prec):
     """Bytes a cell-step cannot do without: the stored state read once and
-    written once. 2D solves with omega = 1 store U (the collision then returns
-    the equilibrium of U), the others every population."""
-    slots = 1 if P.dim == 2 and P.omega == 1.0 else P.Q
+    written once. Solves with omega = 1 store U (the collision then returns the
+    equilibrium of U), the others every population (see keeps_u)."""
+    slots = 1 if keeps_u(P, prec) else P.Q
     return 2 * slots * P.p * (4 if prec == "fp32" else 8)
 
 
@@ -172,14 +177,19 @@ def error_vs_exact(name, P, U, t):
     return None
 
 
-def step_kernel(P, steps):
+def step_kernel(P, prec, steps):
     """The kernel that advances the workload and the steps one launch takes:
-    1D grids of up to 1024 cells (256 for MHD) run up to 1024 steps per
-    launch in one workgroup (k_run1d_wg, the library's rule for its default
-    options); everything else launches k_step1d / k_step2d once per step."""
-    if P.dim == 1 and P.cells <= (256 if P.system == "mhd" else 1024):
-        return "k_run1d_wg", min(1024, steps)
-    return ("k_ustep2d" if P.dim == 2 and P.omega == 1.0 else f"k_step{P.dim}d"), 1
+    small 1D grids run up to 1024 steps per launch in one workgroup (the
+    library's rule for its default options); everything else launches one
+    step at a time. Solves that store U have kernels of their own."""
+    u = keeps_u(P, prec)
+    if P.system == "mhd":
+        small = (768 if prec == "fp32" else 512) if u else 256
+    else:
+        small = 2048 if u and prec == "fp32" else 1024
+    if P.dim == 1 and P.cells <= small:
+        return "k_urun1d" if u else "k_run1d_wg", min(1024, steps)
+    return ("k_ustep" if u else "k_step") + f"{P.dim}d", 1
 
 
 def time_workload(name, prec, K, W):
@@ -221,7 +231,7 @@ def time_workload(name, prec, K, W):
     cells = P.cells
     value = cells * steps * K / (total_ms * 1e-3) / 1e6
     step_time_ms = step_ms / (steps * K)
-    kernel, spl = step_kernel(P, steps)
+    kernel, spl = step_kernel(P, prec, steps)
     abytes = alg_bytes_per_cell_step(P, prec)
     achieved = abytes * cells / (step_time_ms * 1e-3) / 1e9
     two_d = P.dim == 2

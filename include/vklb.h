@@ -133,10 +133,10 @@ typedef struct {
                           (FP32 only; VKLB_ERR_ARG with FP64);
                        0: default: FP64 -> 1; FP32 -> 3 in 1D, 2 in 2D.
                        Other values: VKLB_ERR_ARG.
-                       2D solves with omega = 1 keep U alone between steps (as their basis forms
-                       it: 1 the sum of the populations, 2 and 3 U plus differences), since the
-                       collision then returns the equilibrium of U; vklb_get_state rebuilds the
-                       populations of the basis. */
+                       Solves with omega = 1 (but for 1D FP64 shallow water) keep U alone between
+                       steps (as their basis forms it: 1 the sum of the populations, 2 and 3 U plus
+                       differences), since the collision then returns the equilibrium of U;
+                       vklb_get_state rebuilds the populations of the basis. */
   int band_rows;    /* 2D: rows per workgroup band (MHD in the delta bases: at most 64, larger values
                        are taken as 64); 0 = the default: the tallest power of two from 512 down to
                        4 rows that gives a step at least 2048 wavefronts (two per SIMD); omega = 1:
@@ -147,10 +147,11 @@ typedef struct {
                        always 64 columns per wavefront */
   int halo_rows;    /* 2D: rows of the two halo columns collided per batch (1..32); 0 = tuned default;
                        omega = 1: always 32 */
-  int small_grid;   /* 1D grids of up to 1024 cells (256 for MHD), any boundary condition,
-                       run up to 1024 steps per launch in one workgroup, with bitwise the same
-                       results as one launch per step: 0 = on, 512 lanes (256 for MHD), the fastest
-                       measured; 256, 512 or 1024 = on with that many lanes; -1 = off */
+  int small_grid;   /* 1D grids of up to 1024 cells (256 for MHD; omega = 1: 2048 in FP32, MHD 768 in
+                       FP32 and 512 in FP64), any boundary condition, run up to 1024 steps per
+                       launch in one workgroup, with bitwise the same results as one launch per
+                       step: 0 = on, with the fastest lane count measured; 256, 512 or 1024 = on
+                       with that many lanes where they can hold the grid; -1 = off */
   int fold_partials; /* the per-workgroup maxima a step leaves for the next (max |lambda|, max
                        c_f) are read by every workgroup of the next launch; for a step grid of
                        more than this many workgroups a one-workgroup kernel after each launch
@@ -243,8 +244,9 @@ void vklb_destroy(vklb_solver* s);
  * shape and writes the fastest options to *best (other fields copied from
  * base, which may be NULL) and its time per step to *best_step_us (may be
  * NULL).
- *  - 1D candidates: 256- or 512-lane workgroups; grids of up to 1024 cells
- *    (not MHD) that run in one workgroup: 256, 512 or 1024 lanes.
+ *  - 1D candidates: 256- or 512-lane workgroups (omega = 1: one shape); grids
+ *    of up to 1024 cells (not MHD) that run in one workgroup: 256, 512 or 1024
+ *    lanes.
  *  - 2D candidates: strips of 64/128/256 columns, bands of 4..64 rows, halo
  *    batches of 2, 8, 16 or 32 rows (omega = 1: bands only).
  * All shapes give identical results, so the choice only affects speed. The

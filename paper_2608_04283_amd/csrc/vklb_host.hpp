@@ -7,6 +7,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "../../include/vklb.h"
 #include "vklb_launch.hpp"
 
@@ -138,15 +140,28 @@ inline int default_halo(int kind) { return kind == VKLB_MHD_GLM ? 8 : 32; }
 
 // Solves with omega = 1 keep U alone (vklb_omega1.hpp): the collision then
 // returns the equilibrium of U, so the populations between two steps carry
-// nothing that U does not.
-inline bool keeps_u(int dim, double omega) { return dim == 2 && omega == 1.0; }
+// nothing that U does not. 1D FP64 shallow water keeps its populations, and
+// its every bit: the dam break amplifies a rounding up to 10^8 times at its
+// rarefaction head (reading of its growth in the oracle's tests), so any
+// other rounding would show in its results.
+inline bool keeps_u(int kind, int dim, vklb_precision prec, double omega) {
+  return omega == 1.0 && !(kind == VKLB_SHALLOW_WATER && dim == 1 && prec == VKLB_FP64);
+}
 
-// Workgroups of a 2D step of such a solve (a wavefront per 64 columns and
+// Workgroups of a step of such a solve (2D: a wavefront per 64 columns and
 // `band` rows), and its default band.
 inline long long ustep_waves(const vklb_grid* g, int band) {
   return ((g->n[0] + 63) / 64) * ((g->n[1] + band - 1) / band);
 }
-inline int ustep_grid_of(const vklb_grid* g, int band) {
+// 1D: tiles of 256 cells (a fifth wavefront for the sides) where that takes
+// fewer rounds of one workgroup per compute unit than tiles of 254.
+constexpr long long kCUs = 256;
+inline bool uside_of(const vklb_grid* g) {
+  const long long a = (g->n[0] + utile1d(true) - 1) / utile1d(true), b = (g->n[0] + utile1d(false) - 1) / utile1d(false);
+  return g->dim == 1 && (a + kCUs - 1) / kCUs < (b + kCUs - 1) / kCUs;
+}
+inline int ustep_grid_of(const vklb_grid* g, int band, bool side) {
+  if (g->dim == 1) return int((g->n[0] + utile1d(side) - 1) / utile1d(side));
   return int((ustep_waves(g, band) + kUWaves - 1) / kUWaves);
 }
 // Rows per band of such a step: as few as let every wavefront be resident at
@@ -168,6 +183,15 @@ inline int default_uband(int kind, vklb_precision prec, const vklb_grid* g) {
   const long long rows = ((g->n[0] + 63) / 64 * g->n[1] + waves - 1) / waves;
   const long long most = mhd ? 32 : 16;
   return int(rows < 2 ? 2 : (rows > most ? most : rows));
+}
+
+// Lanes of the one-workgroup kernel of a U solve of n cells: as asked
+// (vklb_options.small_grid) where that many can hold the grid, else the fewest
+// of 256, 512 and 1024 that hold it with the fewest cells a lane.
+inline int uwg_lanes(int kind, long long n, int asked) {
+  const int most = kind == VKLB_MHD_GLM ? 1 : (asked == 256 ? 4 : 2);  // cells per lane
+  if ((asked == 256 || asked == 512 || asked == 1024) && n <= (long long)asked * most) return asked;
+  return n <= 256 ? 256 : (n <= 512 ? 512 : 1024);
 }
 
 inline int step_grid_of(const vklb_grid* g, int width, int band) {
@@ -255,7 +279,7 @@ inline void reorder_rows(const char* from, char* to, const SolveDesc& d, const L
 // Kernel descriptor of a solve whose workspace starts at `base`.
 inline SolveDesc make_desc(char* base, const Layout& L, const vklb_system* sys, const vklb_grid* grid,
                            const vklb_speed* lambda, double omega, const vklb_bc bc[2], const vklb_equilibrium* eq,
-                           int width, int band, int halo) {
+                           int width, int band, int halo, bool batched = false) {
   SolveDesc d;
   memset(&d, 0, sizeof d);
   d.fa = base + L.fa_off;
@@ -297,7 +321,7 @@ inline SolveDesc make_desc(char* base, const Layout& L, const vklb_system* sys, 
   d.nfull = grid->dim == 2 && band > 0 ? int(d.ny / band) : 0;
   d.halo = halo;
   d.nblocks = step_grid_of(grid, width, band);
-  if (keeps_u(grid->dim, omega)) {
+  if (keeps_u(sys->kind, grid->dim, L.elem == 4 ? VKLB_FP32 : VKLB_FP64, omega)) {
     // both U buffers in the first population buffer; the second one is the
     // room for a checkpoint's populations, whose rows are in grid order
     const size_t planes = size_t(L.slots > L.Q ? 2 : 1) * L.p;
@@ -306,7 +330,8 @@ inline SolveDesc make_desc(char* base, const Layout& L, const vklb_system* sys, 
     d.pop = d.fb;
     d.fb = base + L.fa_off + planes * size_t(d.us) * d.ny * L.elem;
     d.nfull = 0;
-    if (grid->dim == 2) d.nblocks = ustep_grid_of(grid, band);
+    d.uside = !batched && uside_of(grid);  // (a batched launch mixes the tiles of many solves)
+    d.nblocks = ustep_grid_of(grid, band, d.uside);
   }
   d.nred = d.nblocks;
   return d;

@@ -83,6 +83,7 @@ struct SolveDesc {
   int nred;              // partials a step launch reduces at entry: nblocks, or 1 when
                          // each launch's partials are folded into entry 0 after it
   int ustate;            // 1: omega = 1, fa and fb hold U alone (vklb_omega1.hpp)
+  int uside;             // U solves, 1D: tiles of 256 cells with a fifth wavefront (ustep1d_tile)
   long long us;          // U buffers: values from one plane of a row to the next
   void* pop;             // U solves: room for the populations of a checkpoint (may be null)
 };
@@ -298,6 +299,25 @@ __device__ inline Step begin_step(const SolveDesc& sd, double* red, int lanes, c
     if (TWO) b = fmax(b, pc[i]);
   }
   block_max2_all<TWO>(a, b, red, lanes);
+  return derive_step(in.S, in.T, in.max_steps, in.err, a, b, sd.ph.ch_factor, sd.xi_mode, sd.nu, sd.xi_fixed, sd.dx);
+}
+
+// Up to 256 partials: every wavefront reads them all, four per lane, and
+// derives the step by itself, without LDS and without a barrier.
+constexpr int kWavePartials = 256;
+template <bool TWO = true>
+__device__ inline void load_partials_wave(const SolveDesc& sd, double& a, double& b) {
+  const gmem<double>* pl = gl(sd.part) + (long long)sd.par * 2 * sd.nblocks;
+  const int last = sd.nred - 1, lane = threadIdx.x & 63;
+  const int i0 = min(lane, last), i1 = min(lane + 64, last), i2 = min(lane + 128, last), i3 = min(lane + 192, last);
+  a = fmax(fmax(pl[i0], pl[i1]), fmax(pl[i2], pl[i3]));
+  pl += sd.nblocks;
+  b = TWO ? fmax(fmax(pl[i0], pl[i1]), fmax(pl[i2], pl[i3])) : 0.0;
+}
+template <bool TWO = true>
+__device__ inline Step begin_step_wave(const SolveDesc& sd, const StateIn& in, double a, double b) {
+  a = wave_max(a);
+  if (TWO) b = wave_max(b);
   return derive_step(in.S, in.T, in.max_steps, in.err, a, b, sd.ph.ch_factor, sd.xi_mode, sd.nu, sd.xi_fixed, sd.dx);
 }
 
@@ -587,8 +607,11 @@ __device__ inline void step1d_tile(const SolveDesc& sd, int tile) {
   K::load(gl((const T*)(bp ? sd.fb : sd.fa)), xl, f);
   K::load_lo(gl((const T*)(bp ? sd.fb : sd.fa)), xl, lo);
   double pa, pb;
-  load_partials<KIND == K_MHD>(sd, B, pa, pb);
-  const Step S = begin_step<KIND == K_MHD>(sd, red, B, in, pa, pb);
+  const bool few = sd.nred <= kWavePartials;
+  if (few) load_partials_wave<KIND == K_MHD>(sd, pa, pb);
+  else load_partials<KIND == K_MHD>(sd, B, pa, pb);
+  const Step S = few ? begin_step_wave<KIND == K_MHD>(sd, in, pa, pb)
+                     : begin_step<KIND == K_MHD>(sd, red, B, in, pa, pb);
   if (S.done) {
     carry_done(sd, S, tile);
     return;
@@ -701,15 +724,18 @@ __global__ void __launch_bounds__(B) k_run1d_wg(const SolveDesc sd, int count) {
   __shared__ T s_plus[P][B * R], s_minus[P][B * R];
   __shared__ T s_unb[2][P];   // characteristic boundaries: U^n of cells 1 and N - 2
   __shared__ double red[2 * (B / 64) + 2];
+  __shared__ int s_bad[B / 64];
   const int N = sd.nx;
   const int tid = threadIdx.x;
   DevState* st = sd.st;
-  // scalars and maxima left by the previous launch (parity sd.par)
-  const Scal s0 = st->S[sd.par];
-  double t = s0.t;
-  long long n = s0.n;
-  int done = s0.done;
-  bool err = st->err_word != ~0ull;
+  // scalars and maxima left by the previous launch (parity sd.par); the end
+  // condition is read once: a load inside the loop would be repeated after
+  // every barrier
+  const StateIn in = read_state(sd);
+  double t = in.S.t;
+  long long n = in.S.n;
+  int done = in.S.done;
+  bool err = in.err;
   double lam = 0.0, cfm = 0.0;
   {
     const double* pl = sd.part + (long long)sd.par * 2 * sd.nblocks;
@@ -739,7 +765,7 @@ __global__ void __launch_bounds__(B) k_run1d_wg(const SolveDesc sd, int count) {
     sc.n = n;
     sc.done = done;
     sc.pad = 0;
-    const Step S = derive_step(sc, st->T, st->max_steps, err, lam, cfm, sd.ph.ch_factor, sd.xi_mode, sd.nu,
+    const Step S = derive_step(sc, in.T, in.max_steps, err, lam, cfm, sd.ph.ch_factor, sd.xi_mode, sd.nu,
                                sd.xi_fixed, sd.dx);
     if (S.done) {
       done = 1;
@@ -823,13 +849,19 @@ __global__ void __launch_bounds__(B) k_run1d_wg(const SolveDesc sd, int count) {
         bad |= K::new_state(sd, Un, c, S.n + 1, lm, cm) ? 1 : 0;
       }
     }
-    // the barriers inside keep the LDS arrays and `red` from being rewritten
-    // by the next step while a lane still reads them
-    err = __syncthreads_or(bad) != 0 || err;
+    // one barrier for the maxima and the non-physical flag; it and the one
+    // above keep the LDS arrays and `red` from being rewritten by the next
+    // step while a lane still reads them
+    if ((tid & 63) == 0) s_bad[tid >> 6] = 0;
+    if (__any(bad) && (tid & 63) == 0) s_bad[tid >> 6] = 1;
     block_max2_all<MHD>(lm, cm, red, B);
+    int mb = 0;
+#pragma unroll
+    for (int w = 0; w < B / 64; ++w) mb |= s_bad[w];
+    err = err || mb != 0;
     lam = lm;
     cfm = cm;
-    t = S.landing ? st->T : S.t + sd.dx / S.xi;
+    t = S.landing ? in.T : S.t + sd.dx / S.xi;
     n = S.n + 1;
   }
   T* __restrict__ dst = (T*)((n & 1) ? sd.fb : sd.fa);

@@ -21,7 +21,7 @@ struct Launchers {
   wg_fn run_wg = nullptr;        // 1D grids of up to wg_max_cells: many steps in one workgroup
   int wg_max_cells = 0;
   int block = 256;  // threads per step workgroup
-  // solves with omega = 1, which keep U alone (ustep null: not built for the dimension)
+  // solves with omega = 1, which keep U alone
   launch_fn ustep = nullptr;
   launch_fn uinit = nullptr;
   launch_fn umoments = nullptr;
@@ -29,6 +29,8 @@ struct Launchers {
   launch_fn upopulate_first = nullptr;  // and before the first one
   launch_fn uextract = nullptr;
   batched_fn ubatched = nullptr;
+  wg_fn urun_wg = nullptr;
+  int uwg_max_cells = 0;
 
   // The launchers of a solve that keeps U, in the places of the others.
   Launchers for_ustate() const {
@@ -37,6 +39,8 @@ struct Launchers {
     L.init_feq = uinit;
     L.moments = umoments;
     L.batched = ubatched;
+    L.run_wg = urun_wg;
+    L.wg_max_cells = uwg_max_cells;
     return L;
   }
 };

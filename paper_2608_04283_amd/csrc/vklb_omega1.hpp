@@ -308,9 +308,352 @@ __global__ void __launch_bounds__(64 * kUWaves) k_ustep2d(const SolveDesc sd) {
   ustep2d_tile<KIND, T, BASIS>(sd, xcd_remap(blockIdx.x, gridDim.x));
 }
 
-// One tile of a solve that keeps U, as step2d_tile for the batched launch.
+// ---------------------------------------------------------------------------
+// Characteristic boundary of a 1D U solve (Sec. 3.3), as step1d_tile applies
+// it: U_b^{n+1} = U_b - P (Lambda dW)' / xi from U^n of the boundary cell and
+// of its interior neighbour `nb`; the cell's populations become the
+// equilibrium of it, whose sum is the new U in the sum form.
+// ---------------------------------------------------------------------------
 template <int KIND, class T, int BASIS>
-__global__ void __launch_bounds__(64 * kUWaves)
+__device__ inline void uchar_state(const SolveDesc& sd, const T* U, const T* nb, bool right, double ixi, double Lam,
+                                   double ch, T* Un, T* fplus, T* rest, T* fminus) {
+  using UK = UKern<KIND, 1, T, BASIS>;
+  constexpr int P = UK::P;
+  T du[P], corr[P];
+#pragma unroll
+  for (int v = 0; v < P; ++v) du[v] = right ? U[v] - nb[v] : nb[v] - U[v];
+  Cell<KIND, 1, T>::char_correction(U, du, sd.ph, T(ch), right, corr);
+#pragma unroll
+  for (int v = 0; v < P; ++v) Un[v] = U[v] - corr[v] * T(ixi);
+  T fe[3][P];
+  Equilibrium<KIND, 1, T>::eval(Un, sd.ph, T(ixi), T(Lam), T(ch), fe);
+#pragma unroll
+  for (int v = 0; v < P; ++v) {
+    if (UK::SUM) Un[v] = ((T(0) + fe[0][v]) + fe[1][v]) + fe[2][v];
+    fplus[v] = fe[0][v];
+    rest[v] = UK::SUM ? fe[1][v] : Un[v];
+    fminus[v] = fe[2][v];
+  }
+}
+
+// New U of a 1D cell from its own equilibria and the populations arriving
+// from the left (a1) and the right (a2).
+template <int KIND, class T, int BASIS>
+__device__ inline void uadvance1d(const SolveDesc& sd, const typename UKern<KIND, 1, T, BASIS>::Pair& pr, double ixi,
+                                  const T* U, const T* lo, const T* fp, const T* fm, const T* net, const T* a1,
+                                  const T* a2, T* Un, T* lo_new) {
+  using UK = UKern<KIND, 1, T, BASIS>;
+  constexpr int P = UK::P;
+  T d[P];
+#pragma unroll
+  for (int v = 0; v < P; ++v) d[v] = (a1[v] - fp[v]) + (a2[v] - fm[v]);
+  if constexpr (UK::PAIR) {
+    if (pr.on) UK::template pair_step<0>(pr, a1[5], a1[8], U[5], U[8], a2[5], a2[8], d[5], d[8]);
+  }
+#pragma unroll
+  for (int v = 0; v < P; ++v) {
+    if (UK::SUM) Un[v] = (a1[v] + UK::rest(U[v], net[v], sd.ph, ixi)) + a2[v];
+    else Un[v] = UK::K::advance(U[v], d[v], lo[v], lo_new[v]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// 1D step: one cell per lane, the populations exchanged through LDS. The cells
+// on either side of a tile are collided by the first and the last of its 256 lanes (254 cells a
+// tile), or (SIDE) by a fifth wavefront (256 cells a tile). The fifth
+// wavefront shares a SIMD with another one, so it pays only where it saves a
+// round of workgroups: 65,536 cells are 256 tiles of 256, one for each compute
+// unit, but 259 of 254, so that three units take two. Euler 65,536 FP64: 4.94
+// us per step with 259 workgroups, 4.09 with 256; MHD 16,384 FP32, 65
+// workgroups or 64, all at once: 5.5 without the fifth wavefront, 6.1 with it.
+// ---------------------------------------------------------------------------
+constexpr int utile1d(bool side) { return side ? 256 : 254; }
+constexpr int ulanes1d(bool side) { return side ? 320 : 256; }
+
+template <int KIND, class T, int BASIS, bool CHARBC, bool SIDE>
+__device__ inline void ustep1d_tile(const SolveDesc& sd, int tile) {
+  using UK = UKern<KIND, 1, T, BASIS>;
+  using K = typename UK::K;
+  constexpr int P = UK::P, B = ulanes1d(SIDE), TW = utile1d(SIDE);
+  constexpr bool MHD = KIND == K_MHD;
+  __shared__ double red[2 * (B / 64) + 2], red_end[2 * (B / 64) + 2];
+  __shared__ T s_plus[P][TW + 2], s_minus[P][TW + 2];  // by position in the tile, its side cells included
+  __shared__ T s_unb[2][P];  // characteristic boundaries: U^n of cells 1 and N - 2
+  const int N = sd.nx;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool side = SIDE && wid == TW / 64;
+  const int x0 = tile * TW;
+  const int x = SIDE ? (side ? (lane == 0 ? x0 - 1 : x0 + TW) : x0 + tid) : x0 - 1 + tid;
+  const bool own = SIDE ? !side : tid >= 1 && tid <= TW;
+  const int xl = map_index(min(x, N), N, sd.bcx);
+  const StateIn in = read_state(sd);
+  const int bp = predicted_parity(sd);
+  T U[P], lo[P];
+  auto load_cell = [&](const gmem<T>* __restrict__ src) {
+    UK::load(src, sd, xl, U);
+#pragma unroll
+    for (int v = 0; v < P; ++v) lo[v] = K::COMP ? src[xl + (long long)(P + v) * sd.us] : T(0);
+  };
+  load_cell(gl((const T*)(bp ? sd.fb : sd.fa)));
+  double pa, pb;
+  const bool few = sd.nred <= kWavePartials;
+  if (few) load_partials_wave<MHD>(sd, pa, pb);
+  else load_partials<MHD>(sd, B, pa, pb);
+  const Step S = few ? begin_step_wave<MHD>(sd, in, pa, pb) : begin_step<MHD>(sd, red, B, in, pa, pb);
+  if (S.done) {
+    carry_done(sd, S, tile);
+    return;
+  }
+  const long long n = S.n;
+  if (int(n & 1) != bp) load_cell(gl((const T*)((n & 1) ? sd.fb : sd.fa)));
+  gmem<T>* __restrict__ dst = gl((T*)((n & 1) ? sd.fa : sd.fb));
+  const double ixi = 1.0 / S.xi, Lam = S.lam, ch = S.ch;
+  const typename UK::Pair pr = UK::pair_of(sd.ph, ixi, Lam, ch);
+  T fp[P], fm[P], net[P];
+  UK::template axis_sent<0>(U, sd.ph, pr, ixi, Lam, ch, fp, fm, net);
+  const int pos = x - x0 + 1;
+  if (!side || lane < 2) {
+#pragma unroll
+    for (int v = 0; v < P; ++v) {
+      s_plus[v][pos] = fp[v];
+      s_minus[v][pos] = fm[v];
+    }
+  }
+  const bool charbc = CHARBC && sd.bcx == 2 && N >= 2;
+  if (charbc && x == 1) {
+#pragma unroll
+    for (int v = 0; v < P; ++v) s_unb[0][v] = U[v];
+  }
+  if (charbc && x == N - 2) {
+#pragma unroll
+    for (int v = 0; v < P; ++v) s_unb[1][v] = U[v];
+  }
+  __syncthreads();
+  double lam = 0.0, cfm = 0.0;
+  if (own && x < N) {
+    T a1[P], a2[P], Un[P], lo_new[P];
+#pragma unroll
+    for (int v = 0; v < P; ++v) {
+      a1[v] = s_plus[v][pos - 1];
+      a2[v] = s_minus[v][pos + 1];
+    }
+    {
+      if (charbc && (x == 0 || x == N - 1)) {
+        T e0[P], e1[P], e2[P];
+        uchar_state<KIND, T, BASIS>(sd, U, s_unb[x == 0 ? 0 : 1], x != 0, ixi, Lam, ch, Un, e0, e1, e2);
+#pragma unroll
+        for (int v = 0; v < P; ++v) lo_new[v] = T(0);
+      } else {
+        uadvance1d<KIND, T, BASIS>(sd, pr, ixi, U, lo, fp, fm, net, a1, a2, Un, lo_new);
+      }
+#pragma unroll
+      for (int v = 0; v < P; ++v) {
+        dst[x + (long long)v * sd.us] = Un[v];
+        if (K::COMP) dst[x + (long long)(P + v) * sd.us] = lo_new[v];
+      }
+      K::new_state(sd, Un, x, n + 1, lam, cfm);
+    }
+  }
+  block_max2<MHD>(lam, cfm, red_end, B);
+  end_step(sd, S, tile, lam, cfm);
+}
+
+template <int KIND, class T, int BASIS, bool CHARBC, bool SIDE>
+__global__ void __launch_bounds__(ulanes1d(SIDE)) k_ustep1d(const SolveDesc sd) {
+  ustep1d_tile<KIND, T, BASIS, CHARBC, SIDE>(sd, blockIdx.x);
+}
+
+// Largest grid that runs in one workgroup, [MHD][FP64]: where a step there
+// still takes less than a launch. us per step, one workgroup / a launch each:
+// Euler FP32 2000 cells 2.95 / 3.4, 2500 3.24 / 3.4; FP64 1000 3.23 / 3.8, 1500
+// 4.10 / 3.9; shallow water FP32 2000 2.38 / 3.4; MHD FP32 700 4.3 / 5.4, 1000
+// 5.5 / 5.5; FP64 500 5.4 / 7.6 (more lanes would spill).
+constexpr int kUWgMax[2][2] = {{2048, 1024}, {768, 512}};
+
+// Max over the wavefront, in every lane, of non-negative values (negatives
+// and NaN count as 0). FP32 values are reduced as FP32: widening is exact.
+__device__ inline float wave_max_t(float v) { return __uint_as_float(wave_umax(__float_as_uint(v >= 0.f ? v : 0.f))); }
+__device__ inline double wave_max_t(double v) { return wave_max(v); }
+
+// ---------------------------------------------------------------------------
+// Small 1D grids: `count` whole steps in one workgroup, as k_run1d_wg, with U
+// in registers. A step meets at two barriers: after the wavefronts' end
+// populations are in LDS, and after their maxima are (with a flag for a
+// non-physical state). 64-cell chunk k = r NW + w is held by wavefront w.
+// Bitwise the results of `count` k_ustep1d launches.
+// ---------------------------------------------------------------------------
+template <int KIND, class T, int BASIS, int R, int B, bool CHARBC>
+__global__ void __launch_bounds__(B) k_urun1d(const SolveDesc sd, int count) {
+  using UK = UKern<KIND, 1, T, BASIS>;
+  using K = typename UK::K;
+  constexpr int P = UK::P, NW = B / 64, NC = R * NW;
+  constexpr bool MHD = KIND == K_MHD;
+  __shared__ T s_p[NC + 1][P], s_m[NC + 1][P];
+  __shared__ T s_unb[2][P];
+  __shared__ T s_lam[NW], s_cf[NW];
+  __shared__ int s_bad[NW];
+  __shared__ double red[2 * NW + 2];
+  const int N = sd.nx;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  gmem<DevState>* st = gl(sd.st);
+  const StateIn in = read_state(sd);
+  const double T_end = in.T;
+  const long long max_steps = in.max_steps;
+  Scal sc = in.S;
+  bool err = in.err;
+  double lam = 0.0, cfm = 0.0;
+  {
+    const gmem<double>* pl = gl(sd.part) + (long long)sd.par * 2 * sd.nblocks;
+    for (int i = tid; i < sd.nblocks; i += B) {
+      lam = fmax(lam, pl[i]);
+      if (MHD) cfm = fmax(cfm, pl[sd.nblocks + i]);
+    }
+    block_max2_all<MHD>(lam, cfm, red, B);
+  }
+  T U[R][P], lo[R][P], Uo[R][P];  // Uo: U of the step before, which a checkpoint's populations are built from
+  {
+    const gmem<T>* __restrict__ src = gl((const T*)((sc.n & 1) ? sd.fb : sd.fa));
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int c = min(r * B + tid, N - 1);  // lanes past the end hold a copy of the last cell
+      UK::load(src, sd, c, U[r]);
+#pragma unroll
+      for (int v = 0; v < P; ++v) lo[r][v] = K::COMP ? src[c + (long long)(P + v) * sd.us] : T(0);
+    }
+  }
+  const bool periodic = sd.bcx == 0, charbc = CHARBC && N >= 2;
+  Step last;
+  bool stepped = false;
+  for (int it = 0; it < count; ++it) {
+    const Step S = derive_step(sc, T_end, max_steps, err, lam, cfm, sd.ph.ch_factor, sd.xi_mode, sd.nu, sd.xi_fixed,
+                               sd.dx);
+    if (S.done) {
+      sc.done = 1;
+      break;
+    }
+    last = S;
+    stepped = true;
+    const double ixi = 1.0 / S.xi, Lam = S.lam, ch = S.ch;
+    const typename UK::Pair pr = UK::pair_of(sd.ph, ixi, Lam, ch);
+    T fp[R][P], fm[R][P], net[R][P];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int k = r * NW + wid, c = r * B + tid;
+      if (r * B + wid * 64 >= N) continue;  // a chunk past the end
+      UK::template axis_sent<0>(U[r], sd.ph, pr, ixi, Lam, ch, fp[r], fm[r], net[r]);
+      if (lane == 0) {
+#pragma unroll
+        for (int v = 0; v < P; ++v) s_m[k][v] = fm[r][v];
+      }
+      if (lane == 63) {
+#pragma unroll
+        for (int v = 0; v < P; ++v) s_p[k + 1][v] = fp[r][v];
+      }
+      if (c == (periodic ? N - 1 : 0)) {  // the left ghost's
+#pragma unroll
+        for (int v = 0; v < P; ++v) s_p[0][v] = fp[r][v];
+      }
+      if (charbc && c == 1) {
+#pragma unroll
+        for (int v = 0; v < P; ++v) s_unb[0][v] = U[r][v];
+      }
+      if (charbc && c == N - 2) {
+#pragma unroll
+        for (int v = 0; v < P; ++v) s_unb[1][v] = U[r][v];
+      }
+    }
+    __syncthreads();
+    double lm = 0.0, cm = 0.0;
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int k = r * NW + wid, c = r * B + tid;
+      if (r * B + wid * 64 >= N) continue;
+      T a1[P], a2[P], Un[P], lo_new[P];
+#pragma unroll
+      for (int v = 0; v < P; ++v) {
+        const T hv = lane < 32 ? s_p[k][v] : s_m[k + 1][v];
+        a1[v] = wave_from_left(fp[r][v], hv);
+        a2[v] = wave_from_right(fm[r][v], hv);
+      }
+      if (c == N - 1) {  // the right ghost's
+#pragma unroll
+        for (int v = 0; v < P; ++v) a2[v] = periodic ? s_m[0][v] : fm[r][v];
+      }
+      if (c < N) {
+        if (charbc && (c == 0 || c == N - 1)) {
+          T e0[P], e1[P], e2[P];
+          uchar_state<KIND, T, BASIS>(sd, U[r], s_unb[c == 0 ? 0 : 1], c != 0, ixi, Lam, ch, Un, e0, e1, e2);
+#pragma unroll
+          for (int v = 0; v < P; ++v) lo_new[v] = T(0);
+        } else {
+          uadvance1d<KIND, T, BASIS>(sd, pr, ixi, U[r], lo[r], fp[r], fm[r], net[r], a1, a2, Un, lo_new);
+        }
+        bad |= K::new_state(sd, Un, c, S.n + 1, lm, cm);
+#pragma unroll
+        for (int v = 0; v < P; ++v) {
+          Uo[r][v] = U[r][v];
+          U[r][v] = Un[v];
+          if (K::COMP) lo[r][v] = lo_new[v];
+        }
+      }
+    }
+    // (lm and cm hold values of T)
+    const T wl = wave_max_t(T(lm)), wc = MHD ? wave_max_t(T(cm)) : T(0);
+    const int wb = __ballot(bad) != 0;
+    if (lane == 0) {
+      s_lam[wid] = wl;
+      if (MHD) s_cf[wid] = wc;
+      s_bad[wid] = wb;
+    }
+    __syncthreads();
+    T ml = T(0), mc = T(0);
+    int mb = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      ml = fmax(ml, s_lam[w]);
+      if (MHD) mc = fmax(mc, s_cf[w]);
+      mb |= s_bad[w];
+    }
+    lam = double(ml);
+    cfm = double(mc);
+    err = err || mb != 0;
+    sc.t = S.landing ? T_end : S.t + sd.dx / S.xi;
+    sc.n = S.n + 1;
+  }
+  gmem<T>* __restrict__ dst = gl((T*)((sc.n & 1) ? sd.fb : sd.fa));
+  gmem<T>* __restrict__ old = gl((T*)((sc.n & 1) ? sd.fa : sd.fb));
+  if (stepped) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int c = r * B + tid;
+      if (c < N) {
+#pragma unroll
+        for (int v = 0; v < P; ++v) {
+          dst[c + (long long)v * sd.us] = U[r][v];
+          old[c + (long long)v * sd.us] = Uo[r][v];
+          if (K::COMP) dst[c + (long long)(P + v) * sd.us] = lo[r][v];
+        }
+      }
+    }
+  }
+  const int pf = sd.par ^ (count & 1);
+  gmem<double>* pl = gl(sd.part) + (long long)pf * 2 * sd.nblocks;
+  for (int i = tid; i < sd.nblocks; i += B) {
+    pl[i] = lam;
+    pl[sd.nblocks + i] = cfm;
+  }
+  if (tid == 0) {
+    store_scal(st, pf, sc);
+    if (stepped) store_last(sd, last);
+  }
+}
+
+// Batched step of the solves that keep U (see k_step_batched).
+template <int KIND, int DIM, class T, int BASIS>
+__global__ void __launch_bounds__(DIM == 1 ? ulanes1d(false) : 64 * kUWaves)
     k_ustep_batched(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ work,
                     const int* __restrict__ nwork, int par) {
   const int i = blockIdx.x;
@@ -318,7 +661,8 @@ __global__ void __launch_bounds__(64 * kUWaves)
   const WorkItem w = work[i];
   SolveDesc sd = descs[w.slot];
   sd.par = par;
-  ustep2d_tile<KIND, T, BASIS>(sd, w.tile);
+  if constexpr (DIM == 1) ustep1d_tile<KIND, T, BASIS, true, false>(sd, w.tile);
+  else ustep2d_tile<KIND, T, BASIS>(sd, w.tile);
 }
 
 // U of step 0 from the staging, and the speeds the populations f^eq(U_0) are
@@ -408,6 +752,21 @@ __global__ void __launch_bounds__(256) k_upopulate(const SolveDesc sd, int first
     const int j = DIM == 2 ? int(c / nx) : 0, i = int(c - (long long)j * nx);
     const long long pc = pcell(sd, c, false);
     T U[P], V[P], fp[P], fm[P], net[P], r[P];
+    if constexpr (DIM == 1) {
+      if (!first && sd.bcx == 2 && nx >= 2 && (i == 0 || i == nx - 1)) {  // a characteristic boundary cell
+        UK::load(old, sd, i, U);
+        UK::load(old, sd, i == 0 ? 1 : nx - 2, V);
+        uchar_state<KIND, T, BASIS>(sd, U, V, i != 0, ixi, Lam, ch, net, fp, r, fm);
+#pragma unroll
+        for (int v = 0; v < P; ++v) {
+          f[K::pidx(0 * P + v, pc)] = fp[v];
+          f[K::pidx(1 * P + v, pc)] = r[v];
+          f[K::pidx(2 * P + v, pc)] = fm[v];
+          if (K::COMP) f[K::pidx(Q * P + v, pc)] = T(0);
+        }
+        continue;
+      }
+    }
     if (UK::SUM) {  // rest population of the cell itself
       UK::load(old, sd, UK::row(sd, j) + i, V);
       UK::template axis<0>(V, sd.ph, ixi, Lam, ch, fp, fm, r);

@@ -256,7 +256,7 @@ vklb_status admit(vklb_pool* p) {
     p->slots[slot] = r;
     const int width = r->grid.dim == 1 ? 256 : 128;  // the batched kernels' tile widths
     r->sd = make_desc(p->base + off, r->L, &r->sys, &r->grid, &r->speed, r->omega, r->bc, &r->eq, width, r->band,
-                      r->halo);
+                      r->halo, true);
     r->sd.pop = nullptr;  // the pool takes no checkpoints
     r->sd.npar = int(p->round & 1);  // step 0 runs at the parity of the next round
     if (r->sd.nblocks > kFoldAbove) r->sd.nred = 1;  // as a single solve: partials folded after each round
@@ -398,7 +398,7 @@ vklb_status vklb_pool_submit(vklb_pool* p, const vklb_request* rq, uint64_t* tic
   const long long cells = r->grid.n[0] * (r->grid.dim == 2 ? r->grid.n[1] : 1);
   r->U0.assign(rq->U0, rq->U0 + size_t(r->L.p) * cells);
   r->U_out = rq->U_out;
-  const bool ust = keeps_u(r->grid.dim, r->omega);
+  const bool ust = keeps_u(r->sys.kind, r->grid.dim, p->prec, r->omega);
   r->cls = class_of(r->sys.kind, r->grid.dim, ust);
   r->band = 32;
   if (r->grid.dim == 2)  // the batched 2D strips are 128 columns, a U solve's 64
@@ -577,7 +577,7 @@ vklb_status vklb_pool_autotune(vklb_pool* p, const vklb_request* samples, int n,
     if (st != VKLB_OK) return pfail(p, st, std::string("vklb_pool_autotune: ") + vklb_last_error(nullptr));
     {
       std::lock_guard<std::mutex> lk(g_tiles_mu);
-      g_tiles[{p->device, int(p->prec), int(r.sys.kind), int(keeps_u(2, r.omega)), size_class(r.grid.n[0])}] = {band,
+      g_tiles[{p->device, int(p->prec), int(r.sys.kind), int(keeps_u(r.sys.kind, 2, p->prec, r.omega)), size_class(r.grid.n[0])}] = {band,
                                                                                                               halo};
     }
     if (out && n_out && written < *n_out) {

@@ -409,7 +409,7 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
     width = default_width(grid->dim, grid->n[0]);
   pl->width = width;
   pl->K = pick_launchers(sys->kind, grid->dim, prec == VKLB_FP32 ? 1 : 0, pl->basis, width);
-  const bool ust = keeps_u(grid->dim, omega);
+  const bool ust = keeps_u(sys->kind, grid->dim, prec, omega);
   if (ust) pl->K = pl->K.for_ustate();
   int band = o.band_rows;
   if (band < 1) band = ust ? default_uband(sys->kind, prec, grid) : default_band(grid, width);
@@ -423,8 +423,7 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
   // nblocks^2 loads per step (10^12 at a million workgroups), so above the
   // threshold each launch's partials are folded into one entry instead.
   const int fold = o.fold_partials == 0 ? kFoldAbove : o.fold_partials;
-  pl->nred_one = fold > 0 && (ust && grid->dim == 2 ? ustep_grid_of(&pl->grid, band)
-                                                    : step_grid_of(&pl->grid, width, band)) > fold;
+  pl->nred_one = fold > 0 && (ust ? ustep_grid_of(&pl->grid, band, uside_of(&pl->grid)) : step_grid_of(&pl->grid, width, band)) > fold;
   // small 1D grids: whole step sequences in one workgroup (bitwise the same)
   pl->wg_cells = pl->wg_lanes = 0;
   if (grid->dim == 1 && o.small_grid >= 0 && pl->K.run_wg && grid->n[0] <= pl->K.wg_max_cells) {
@@ -434,8 +433,9 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
     int lanes = o.small_grid;
     if (lanes != 256 && lanes != 512 && lanes != 1024) lanes = 512;
     if (sys->kind == VKLB_MHD_GLM) lanes = 256;
+    if (ust) lanes = uwg_lanes(sys->kind, n, o.small_grid);
     int cells = int((n + lanes - 1) / lanes);
-    if (cells == 3) cells = 4;
+    if (cells == 3 && lanes < 1024) cells = 4;
     pl->wg_lanes = lanes;
     pl->wg_cells = cells;
   }
@@ -796,7 +796,7 @@ static vklb_status tune_impl(const vklb_system* sys, vklb_lattice lat, const vkl
   // candidate tile shapes
   std::vector<vklb_options> cand;
   // a solve that keeps U has one strip width and one halo batch
-  const bool ust = keeps_u(grid->dim, omega);
+  const bool ust = keeps_u(sys->kind, grid->dim, prec, omega);
   if (pool_2d) {
     const long long ny = grid->n[1];
     for (int band : {4, 8, 16, 32, 64}) {
@@ -812,6 +812,7 @@ static vklb_status tune_impl(const vklb_system* sys, vklb_lattice lat, const vkl
     }
   } else if (grid->dim == 1) {
     for (int w : {256, 512}) {
+      if (ust && w > 256) continue;
       vklb_options o = b0;
       o.strip_width = w;
       cand.push_back(o);

@@ -77,8 +77,10 @@ def tune_shapes(precision="fp32", steps=20, seed=11, sizes=TUNE_SIZES):
 
 def _alg_bytes(prob, precision):
     """Algorithmic bytes of one cell-step: the stored state read once and
-    written once (2D with omega = 1: U, 2 p s; else every population, 2 Q p s)."""
-    slots = 1 if prob.dim == 2 and prob.omega == 1.0 else prob.Q
+    written once (omega = 1: U, 2 p s; else, and in 1D FP64 shallow water,
+    every population, 2 Q p s)."""
+    u = prob.omega == 1.0 and not (prob.system == "sw" and prob.dim == 1 and precision == "fp64")
+    slots = 1 if u else prob.Q
     return 2 * slots * prob.p * (4 if precision == "fp32" else 8)
 
 

@@ -31,6 +31,12 @@ def state2d(system, nx, ny, seed, **kw):
                      **kw)
 
 
+def state1d(system, n, seed, **kw):
+    P = state2d(system, n, 1, seed)
+    U0 = P.U0 if system == "mhd" else np.delete(P.U0, 2, axis=0)  # no v in 1D
+    return P.with_(dim=1, n=(n,), hi=(1.0, 1.0), nu=0.8, U0=U0, **kw)
+
+
 def run(gpu, P, prec, steps, **opts):
     s = gpu.Solver(P, precision=prec, **opts)
     s.init()
@@ -74,6 +80,48 @@ def test_2d_agrees_with_the_path_that_stores_populations(gpu, system, prec, bc):
             a = run(gpu, P, prec, steps, **opts)
             b = run(gpu, P.with_(omega=1.0 + 2.0 ** -52), prec, steps, **opts)
             agree(P, prec, steps, a, b)
+
+
+# one workgroup (1 and 2 cells a lane, partly filled wavefronts), tiles of 254
+# cells and their edges, more partials than a wavefront reads, tiles of 256
+SIZES = [1, 2, 3, 64, 65, 254, 256, 257, 511, 1000, 2048, 2049, 3000, 65100, 65536, 70000]
+
+
+@pytest.mark.parametrize("bc", ["periodic", "zero_gradient", "characteristic"])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("system", ["sw", "euler", "mhd"])
+def test_1d_agrees_with_the_path_that_stores_populations(gpu, system, prec, bc):
+    for k, n in enumerate(SIZES):
+        if bc == "characteristic" and n < 2:
+            continue
+        for steps, opts in ((0, {}), (1, {}), (14, {}), (15, {"small_grid": -1}), (6, {"basis": 2}),
+                            (5, {"basis": 1, "small_grid": 1024})):
+            P = state1d(system, n, 40 + k, bc=(bc, bc), alpha_norm="local" if k % 3 == 2 else "global")
+            print(f"[case] {system} {n} {prec} {bc} steps={steps} {opts}", flush=True)
+            a = run(gpu, P, prec, steps, **opts)
+            b = run(gpu, P.with_(omega=1.0 + 2.0 ** -52), prec, steps, **opts)
+            agree(P, prec, steps, a, b)
+
+
+@pytest.mark.parametrize("system,prec", [("euler", "fp32"), ("euler", "fp64"), ("mhd", "fp32"), ("sw", "fp32")])
+@pytest.mark.parametrize("bc", ["periodic", "characteristic"])
+def test_1d_checkpoints_between_the_one_workgroup_kernel_and_launches(gpu, system, prec, bc):
+    for n in (2, 200, 700, 1500):
+        P = state1d(system, n, 7, bc=(bc, bc))
+        ref = run(gpu, P, prec, 21)
+        for first, second in ((0, -1), (-1, 0), (512, 1024)):
+            a = gpu.Solver(P, precision=prec, small_grid=first)
+            a.init()
+            a.step(10)
+            blob, _, _ = a.get_state()
+            a.close()
+            b = gpu.Solver(P, precision=prec, small_grid=second)
+            b.set_state(blob)
+            assert np.array_equal(b.get_state()[0], blob)
+            b.step(11)
+            U, t, steps = b.moments()
+            b.close()
+            assert steps == 21 and t == ref[1] and np.array_equal(U, ref[0]), (n, first, second)
 
 
 @pytest.mark.parametrize("basis", [1, 2, 3])
