@@ -82,6 +82,16 @@ __host__ __device__ inline S qsqrt(S x) {
   return sqrt(x);
 }
 
+// Positive and finite: one class test on the device.
+template <class S>
+__host__ __device__ inline bool positive_finite(S x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (sizeof(S) == 4) return __builtin_amdgcn_classf(x, 0x180);  // + subnormal, + normal
+  else return __builtin_amdgcn_class(x, 0x180);
+#endif
+  return x > S(0) && isfinite(x);
+}
+
 // tanh for the weights. FP32 device code evaluates it from its exponential
 // form, tanh z = sign(z) (1 - e^{-2|z|}) / (1 + e^{-2|z|}), with the hardware
 // base-2 exponential and reciprocal: a few units in the last place (absolute
@@ -113,31 +123,30 @@ __host__ __device__ inline S beta_w(S lam, S half_k_over_L, int kinf) {
 // beta of N speeds of one direction, none larger than lmax in magnitude. With
 // the sigmoid normalized by the largest |lambda| and k <= 2 (Sec. 3.1, k = 2)
 // every argument z = k lambda / (2 Lambda) lies in [-1, 1], where tanh(z) / 2 is
-// an odd polynomial, z p(z^2): 9 vector operations a weight in FP32 (degree 7)
-// and 17 in FP64 (degree 15), with no transcendental one among them, against
+// an odd polynomial, z p(z^2): 9 vector operations a weight in FP32 (degree 6)
+// and 18 in FP64 (degree 15), with no transcendental one among them, against
 // 11 and about 85 of wtanh. The coefficients are the interpolant of
 // tanh(sqrt w) / (2 sqrt w) at Chebyshev nodes of [0, 1.0414]; relative error
-// 1.1e-7 and 2.2e-16 over |z| <= 1.02, rounding included (wtanh in FP32: 1.6e-6
-// relative for |z| > 0.01, 6.5e-8 absolute against 4.3e-8 here). Larger
+// 1.6e-7 and 2.2e-16 over |z| <= 1.02, rounding included (wtanh in FP32: 1.6e-6
+// relative for |z| > 0.01, 6.5e-8 absolute against 5.9e-8 here). Larger
 // arguments (k > 2, or a boundary state faster than the grid) take wtanh.
 template <class S, int N>
 __host__ __device__ inline void weights(const S (&lam)[N], S lmax, S hk, int kinf, S (&b)[N]) {
   if (!kinf && lmax * hk <= S(1.02)) {
-    constexpr double c32[8] = {0.5, -0.16666631400585175, 0.06665942817926407, -0.02692667953670025,
-                               0.010705825872719288, -0.0039176070131361485, 0.0011097308015450835,
-                               -0.00016730035713408142};
+    constexpr double c32[7] = {0.4999999701976776, -0.16666358709335327, 0.06661827117204666, -0.026692891493439674,
+                               0.010071528144180775, -0.0030323248356580734, 0.0004960894584655762};
     constexpr double c64[16] = {0.5, -0.16666666666666183, 0.06666666666626553, -0.02698412697101095,
                                 0.010934744042573333, -0.004431615413343778, 0.001796047850046346,
                                 -0.0007278399231292868, 0.0002947479495034335, -0.00011889149097278873,
                                 4.718446560211916e-05, -1.7825235404940583e-05, 6.004817950962269e-06,
                                 -1.6264485337714894e-06, 3.023335014179045e-07, -2.7998503351044707e-08};
-    constexpr int n = sizeof(S) == 4 ? 7 : 15;
+    constexpr int n = sizeof(S) == 4 ? 6 : 15;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       const S z = lam[j] * hk, w = z * z;
-      S p = S(sizeof(S) == 4 ? c32[7] : c64[15]);
+      S p = S(sizeof(S) == 4 ? c32[6] : c64[15]);
 #pragma unroll
-      for (int i = n - 1; i >= 0; --i) p = p * w + S(sizeof(S) == 4 ? c32[i & 7] : c64[i]);
+      for (int i = n - 1; i >= 0; --i) p = p * w + S(sizeof(S) == 4 ? c32[i % 7] : c64[i]);
       b[j] = p * z;
     }
   } else {
@@ -244,13 +253,13 @@ struct Cell<K_SW, DIM, S> {
     const S lm = ud - c, lp = ud + c;
     const S L = ph.alpha_local ? fmax(fabs(lm), fabs(lp)) : Lam;
     const S hk = L > S(0) ? qdiv(S(0.5 * ph.k), L) : S(0);
-    // The weights' polynomial (weights) is not used here except in 2D FP64. In
-    // FP32 the range check costs what it saves on two weights (a 100-cell solve
-    // in one workgroup: 1.39 us a step with it, 1.33 without). The 1D FP64
-    // results stay bit for bit: the dam break amplifies a rounding up to 10^8
-    // times at its rarefaction head, so any other rounding shows in them.
+    // The weights' polynomial (weights) is used in 2D. In 1D FP32 its range
+    // check costs what it saves on two weights (a 100-cell solve in one
+    // workgroup: 1.39 us a step with it, 1.33 without). The 1D FP64 results
+    // stay bit for bit: the dam break amplifies a rounding up to 10^8 times at
+    // its rarefaction head, so any other rounding shows in them.
     S b[2];
-    if (DIM == 2 && sizeof(S) == 8) {
+    if (DIM == 2) {
       const S lam[2] = {lm, lp};
       weights(lam, S(fmax(fabs(lm), fabs(lp))), hk, ph.kinf, b);
     } else {
@@ -312,9 +321,8 @@ struct Cell<K_EULER, DIM, S> {
     *cfm = S(0);
   }
   __host__ __device__ static bool admissible(const S* U, const Phys& ph) {
-    bool ok = U[0] > S(0) && pressure(U, S(ph.gamma)) > S(0);
-    for (int i = 0; i < P; ++i) ok = ok && isfinite(U[i]);
-    return ok;
+    // p takes in every other field: an infinite or NaN one makes it so
+    return positive_finite(U[0]) && positive_finite(pressure(U, S(ph.gamma)));
   }
   __host__ __device__ static void split(int d, const S* U, const Phys& ph, S Lam, S, S* F, S* D) {
     const S gamma = S(ph.gamma);
@@ -472,9 +480,8 @@ struct Cell<K_MHD, DIM, S> {
     *cfm = cm;
   }
   __host__ __device__ static bool admissible(const S* U, const Phys& ph) {
-    bool ok = U[0] > S(0) && pressure(U, S(ph.gamma)) > S(0);
-    for (int i = 0; i < P; ++i) ok = ok && isfinite(U[i]);
-    return ok;
+    // p takes in every other field but psi: an infinite or NaN one makes it so
+    return positive_finite(U[0]) && positive_finite(pressure(U, S(ph.gamma))) && isfinite(U[8]);
   }
 
   // Primitive-variable wave decomposition along the normal direction.
@@ -635,17 +642,16 @@ struct Cell<K_MHD, DIM, S> {
     //   x_C = (0, -gamma B_n / rho, -B_t / rho, 0, (gamma - 1) B_t v_t, -v_t, -v_q).
     const S vp = e.by * v + e.bz * w, vq = e.by * w - e.bz * v;
     const S ia = qrcp(e.a), ia2 = ia * ia, sr = qsqrt(rho), isr = sr * irho;
-    const S bt = e.bt, ia2r = ia2 * irho, ias = ia * isr;
+    const S bt = e.bt, h2 = S(0.5) * ia2, h2r = h2 * irho, has = S(0.5) * ia * isr, hsr = S(0.5) * isr;
     const S afcf = e.af * e.cf, ascs = e.as * e.cs;
     struct Coef {
       S fm, fp, sm, sp, a, e;  // f-, f+, s-, s+, a- = a+, entropy
     };
     auto expand = [&](S x0, S x1, S xvp, S x4, S xbp, S xbq) {
-      const S X = x4 * ia2r, Y = xbp * ias, Z2 = sgn * xvp;
+      const S X = x4 * h2r, Y = xbp * has, Z1 = x1 * h2, Z2 = sgn * xvp * h2;  // halves of the coefficients' sums
       const S Fp = e.af * X + e.as * Y, Sp = e.as * X - e.af * Y;
-      const S Fm = (afcf * x1 - ascs * Z2) * ia2, Sm = (ascs * x1 + afcf * Z2) * ia2;
-      return Coef{S(0.5) * (Fp - Fm), S(0.5) * (Fp + Fm), S(0.5) * (Sp - Sm), S(0.5) * (Sp + Sm),
-                  S(0.5) * (xbq * isr), x0 - x4 * ia2};
+      const S Fm = afcf * Z1 - ascs * Z2, Sm = ascs * Z1 + afcf * Z2;
+      return Coef{Fp - Fm, Fp + Fm, Sp - Sm, Sp + Sm, xbq * hsr, x0 - x4 * ia2};
     };
     const S x4c = gm1 * (bt * vp), x4f = u * p + gm1 * (S(0.5) * u * (Bn * Bn - bt * bt)) + Bn * x4c;
     const Coef f = expand(F[0], (pt - Bn * Bn) * irho, -Bn * bt * irho, x4f, u * bt - Bn * vp, -Bn * vq);

@@ -496,7 +496,22 @@ struct Kern {
     }
   }
 
-  // Delta bases, 2D: post-collision population of velocity +AXIS (plus) or
+  // 2D: U of a cell from its stored values, as relax takes it.
+  __device__ static inline void moments_reg(const T (&f)[Q][P], T (&U)[P]) {
+#pragma unroll
+    for (int v = 0; v < P; ++v) {
+      if (DELTA) {
+        U[v] = f[REST][v];
+      } else {
+        T s = T(0);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) s += f[q][v];
+        U[v] = s;
+      }
+    }
+  }
+
+  // 2D: post-collision population of velocity +AXIS (plus) or
   // -AXIS from U and that population alone, with the split of that axis
   // only; bitwise what relax gives for it.
   template <int AXIS>
@@ -554,18 +569,11 @@ struct Kern {
     }
   }
 
-  template <class SP>
-  __device__ static inline void collide(SP __restrict__ src, long long cell, const Phys& ph, double ixi,
-                                        double Lam, double ch, T (&fs)[Q][P], T (&U)[P]) {
-    T f[Q][P];
-    load(src, cell, f);
-    relax(f, ph, ixi, Lam, ch, fs, U);
-  }
-
-  // Speeds of a finished cell for the global maxima; flags non-physical
-  // states (the error word, and the return value).
-  __device__ static inline bool new_state(const SolveDesc& sd, const T (&U)[P], long long cell, long long step,
-                                          double& lam, double& cfm) {
+  // Speeds of a finished cell for the global maxima (of type double or T);
+  // flags non-physical states (the error word, and the return value).
+  template <class M>
+  __device__ static inline bool new_state(const SolveDesc& sd, const T (&U)[P], long long cell, long long step, M& lam,
+                                          M& cfm) {
     ST Us[P];
 #pragma unroll
     for (int v = 0; v < P; ++v) Us[v] = ST(U[v]);
@@ -577,8 +585,8 @@ struct Kern {
       l = ST(0);
       c = ST(0);
     }
-    lam = fmax(lam, double(l));
-    cfm = fmax(cfm, double(c));
+    lam = fmax(lam, M(l));
+    cfm = fmax(cfm, M(c));
     return bad;
   }
 };
@@ -950,9 +958,11 @@ __device__ inline void step2d_tile_rows(const SolveDesc& sd, int tile) {
   // Rows whose loads are in flight ahead of the one being collided (SW and
   // Euler): each lane keeps this many rows of stored values in registers.
   constexpr int AHEAD = PREFETCH ? 2 : 0;
-  // In the delta bases the rows next to the band and the halo columns use one
-  // population each: they load only U and that population and collide it with
-  // the split of its axis alone.
+  // The rows next to the band and the halo columns use one population each:
+  // it is collided with the split of its axis alone, and in the delta bases
+  // only it and U are loaded (else every population makes up U; FP64 Euler
+  // 512^2, whose 4-row bands collide as many such rows as half their own: 22.7
+  // -> 22.4 us per step).
   constexpr bool PARTIAL = DELTA;
   // The row before the band in march order streams one population into its
   // first row (y0 - 1: +y up; y1: -y down); the row after it, into its last.
@@ -1005,10 +1015,12 @@ __device__ inline void step2d_tile_rows(const SolveDesc& sd, int tile) {
   T prevm[P];
   if (PARTIAL) {
     K::template relax_one<1>(fpre[REST], fpre[3], !down, sd.ph, ixi, Lam, ch, prevm);
-  } else {
-    K::relax(fpre, sd.ph, ixi, Lam, ch, fs, U);
+  } else {  // every population makes up U, but one axis is split
+    T fq[P];
+    K::moments_reg(fpre, U);
 #pragma unroll
-    for (int v = 0; v < P; ++v) prevm[v] = down ? fs[4][v] : fs[3][v];
+    for (int v = 0; v < P; ++v) fq[v] = down ? fpre[4][v] : fpre[3][v];
+    K::template relax_one<1>(U, fq, !down, sd.ph, ixi, Lam, ch, prevm);
   }
   // Values of the previous row (march order) carried into the next iteration.
   T c_rest[P], c4[P], c5[P], c_lo[P];
@@ -1072,10 +1084,14 @@ __device__ inline void step2d_tile_rows(const SolveDesc& sd, int tile) {
 #pragma unroll
           for (int v = 0; v < P; ++v) s_halo[buf][side][tid & 31][v] = hs[v];
         } else {
-          T hf[Q][P], hU[P];
-          K::collide(src, hrow + hx, sd.ph, ixi, Lam, ch, hf, hU);
+          T hf[Q][P], hU[P], hq[P], hs[P];
+          K::load(src, hrow + hx, hf);
+          K::moments_reg(hf, hU);
 #pragma unroll
-          for (int v = 0; v < P; ++v) s_halo[buf][side][tid & 31][v] = side == 0 ? hf[0][v] : hf[1][v];
+          for (int v = 0; v < P; ++v) hq[v] = side == 0 ? hf[0][v] : hf[1][v];
+          K::template relax_one<0>(hU, hq, side == 0, sd.ph, ixi, Lam, ch, hs);
+#pragma unroll
+          for (int v = 0; v < P; ++v) s_halo[buf][side][tid & 31][v] = hs[v];
         }
       }
     }
@@ -1151,7 +1167,13 @@ __device__ inline void step2d_tile_rows(const SolveDesc& sd, int tile) {
       for (int v = 0; v < P; ++v) fs[4][v] = fs[3][v];
     }
   } else {
-    K::relax(fraw, sd.ph, ixi, Lam, ch, fs, U);
+    T fq[P];
+    K::moments_reg(fraw, U);
+#pragma unroll
+    for (int v = 0; v < P; ++v) fq[v] = down ? fraw[3][v] : fraw[4][v];
+    K::template relax_one<1>(U, fq, down, sd.ph, ixi, Lam, ch, fs[4]);
+#pragma unroll
+    for (int v = 0; v < P; ++v) fs[3][v] = fs[4][v];
   }
   if (x < nx) finish(nr - 1);
   block_max2<KIND == K_MHD>(lam, cfm, red_end, W);

@@ -42,17 +42,6 @@ __device__ inline double wave_shift64(double v, double edge) {
 __device__ inline double wave_from_left(double v, double edge) { return wave_shift64<0x138>(v, edge); }
 __device__ inline double wave_from_right(double v, double edge) { return wave_shift64<0x130>(v, edge); }
 
-// Lane 63's value, in every lane (all lanes active).
-__device__ inline float wave_last(float v) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-__device__ inline double wave_last(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, 63);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), 63);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 template <int KIND, int DIM, class T, int BASIS>
 struct UKern {
   using K = Kern<KIND, DIM, T, BASIS>;
@@ -189,8 +178,10 @@ __device__ inline void ustep2d_tile(const SolveDesc& sd, int tile) {
   };
   load_first();
   double pa, pb;
-  load_partials<MHD>(sd, W, pa, pb);
-  const Step S = begin_step<MHD>(sd, red, W, in, pa, pb);
+  const bool few = sd.nred <= kWavePartials;
+  if (few) load_partials_wave<MHD>(sd, pa, pb);
+  else load_partials<MHD>(sd, W, pa, pb);
+  const Step S = few ? begin_step_wave<MHD>(sd, in, pa, pb) : begin_step<MHD>(sd, red, W, in, pa, pb);
   if (S.done) {
     carry_done(sd, S, tile);
     return;
@@ -203,7 +194,7 @@ __device__ inline void ustep2d_tile(const SolveDesc& sd, int tile) {
   gmem<T>* __restrict__ dst = gl((T*)((n & 1) ? sd.fa : sd.fb));
   const double ixi = 1.0 / S.xi, Lam = S.lam, ch = S.ch;
   const typename UK::Pair pr = UK::pair_of(sd.ph, ixi, Lam, ch);
-  double lam = 0.0, cfm = 0.0;
+  T lamT = T(0), cfT = T(0);  // (widened after the march: exact)
   if (active) {
     T prevm[P];  // +y equilibrium of the row below the one being collided
     {
@@ -211,20 +202,26 @@ __device__ inline void ustep2d_tile(const SolveDesc& sd, int tile) {
       UK::template axis_sent<1>(preU, sd.ph, pr, ixi, Lam, ch, prevm, fm, net);
     }
     // Of the row waiting for the row above it: the sum so far (sum form) or
-    // U, the x and +y differences and its own -y equilibrium (delta forms).
-    T cU[P], cX[P], cY[P], c5[P], clo[P];
+    // U, the x and +y differences (cD) and its own -y equilibrium (c5); of
+    // MHD's cleaning pair, the row below's B_y and psi (cB, cP).
+    T cU[P], cD[P], c5[P], clo[P], cB = T(0), cP = T(0);
     auto finish = [&](int j, const T(&ym)[P]) {
       const int r = y0 + j;
-      T Un[P], lo_new[P], dY[P];
+      T Un[P], lo_new[P], d[P];
 #pragma unroll
-      for (int v = 0; v < P; ++v) dY[v] = UK::SUM ? T(0) : cY[v] + (ym[v] - c5[v]);
+      for (int v = 0; v < P; ++v) d[v] = UK::SUM ? T(0) : cD[v] + (ym[v] - c5[v]);
       if constexpr (UK::PAIR) {
-        if (pr.on) UK::template pair_step<1>(pr, cY[6], cY[8], c5[6], c5[8], ym[6], ym[8], dY[6], dY[8]);
+        if (pr.on) {
+          T dB, dP;
+          UK::template pair_step<1>(pr, cB, cP, cU[6], cU[8], ym[6], ym[8], dB, dP);
+          d[6] = cD[6] + dB;
+          d[8] = cD[8] + dP;
+        }
       }
 #pragma unroll
       for (int v = 0; v < P; ++v) {
         if (UK::SUM) Un[v] = cU[v] + ym[v];
-        else Un[v] = K::advance(cU[v], cX[v] + dY[v], clo[v], lo_new[v]);
+        else Un[v] = K::advance(cU[v], d[v], clo[v], lo_new[v]);
       }
       if (lane < nvalid) {
         gmem<T>* p = dst + UK::row(sd, r) + x0;
@@ -233,7 +230,7 @@ __device__ inline void ustep2d_tile(const SolveDesc& sd, int tile) {
           p[v * us + lc] = Un[v];
           if (K::COMP) p[(P + v) * us + lc] = lo_new[v];
         }
-        K::new_state(sd, Un, (long long)r * nx + x0 + lane, n + 1, lam, cfm);
+        K::new_state(sd, Un, (long long)r * nx + x0 + lane, n + 1, lamT, cfT);
       }
     };
     for (int i = 0; i < nr; ++i) {
@@ -248,12 +245,13 @@ __device__ inline void ustep2d_tile(const SolveDesc& sd, int tile) {
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       }
-      T U[P], lo[P], hv[P];
+      T U[P], lo[P], hl[P], hr[P];
 #pragma unroll
       for (int v = 0; v < P; ++v) {
         U[v] = nU[v];
         lo[v] = nlo[v];
-        hv[v] = s_halo[wid][hside][i & 31][v];
+        hl[v] = s_halo[wid][0][i & 31][v];
+        hr[v] = s_halo[wid][1][i & 31][v];
       }
       if (i + 1 < nr) {
         load_row(y0 + i + 1, nU);
@@ -269,27 +267,33 @@ __device__ inline void ustep2d_tile(const SolveDesc& sd, int tile) {
       T a1[P], a2[P];
 #pragma unroll
       for (int v = 0; v < P; ++v) {
-        a1[v] = wave_from_left(fp0[v], hv[v]);
-        a2[v] = wave_from_right(fm0[v], hv[v]);
-        if (last != 63) {
-          const T e = wave_last(hv[v]);
-          a2[v] = lane == last ? e : a2[v];
-        }
+        a1[v] = wave_from_left(fp0[v], hl[v]);
+        a2[v] = wave_from_right(fm0[v], hr[v]);
+      }
+      if (last != 63) {
+#pragma unroll
+        for (int v = 0; v < P; ++v) a2[v] = lane == last ? hr[v] : a2[v];
+      }
+#pragma unroll
+      for (int v = 0; v < P; ++v) {
         if (UK::SUM) {
           cU[v] = ((a1[v] + a2[v]) + UK::rest(U[v], net0[v] + net1[v], sd.ph, ixi)) + prevm[v];
         } else {
           cU[v] = U[v];
-          cX[v] = (a1[v] - fp0[v]) + (a2[v] - fm0[v]);
-          cY[v] = prevm[v] - fp1[v];
+          cD[v] = ((a1[v] - fp0[v]) + (a2[v] - fm0[v])) + (prevm[v] - fp1[v]);
           c5[v] = fm1[v];
           clo[v] = lo[v];
         }
       }
       if constexpr (UK::PAIR) {
         if (pr.on) {
-          UK::template pair_step<0>(pr, a1[5], a1[8], U[5], U[8], a2[5], a2[8], cX[5], cX[8]);
-          cY[6] = prevm[6];  // the row below's own values, until the row above is known
-          cY[8] = prevm[8];
+          T dB, dP;
+          UK::template pair_step<0>(pr, a1[5], a1[8], U[5], U[8], a2[5], a2[8], dB, dP);
+          cD[5] = dB + (prevm[5] - fp1[5]);
+          cD[6] = (a1[6] - fp0[6]) + (a2[6] - fm0[6]);
+          cD[8] = dP;
+          cB = prevm[6];
+          cP = prevm[8];
         }
       }
 #pragma unroll
@@ -299,6 +303,7 @@ __device__ inline void ustep2d_tile(const SolveDesc& sd, int tile) {
     UK::template axis_sent<1>(nU, sd.ph, pr, ixi, Lam, ch, fp, fm, net);
     finish(nr - 1, fm);
   }
+  double lam = double(lamT), cfm = double(cfT);
   block_max2<MHD>(lam, cfm, red_end, W);
   end_step(sd, S, tile, lam, cfm);
 }
@@ -565,7 +570,7 @@ __global__ void __launch_bounds__(B) k_urun1d(const SolveDesc sd, int count) {
       }
     }
     __syncthreads();
-    double lm = 0.0, cm = 0.0;
+    T lm = T(0), cm = T(0);
     bool bad = false;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -600,8 +605,7 @@ __global__ void __launch_bounds__(B) k_urun1d(const SolveDesc sd, int count) {
         }
       }
     }
-    // (lm and cm hold values of T)
-    const T wl = wave_max_t(T(lm)), wc = MHD ? wave_max_t(T(cm)) : T(0);
+    const T wl = wave_max_t(lm), wc = MHD ? wave_max_t(cm) : T(0);
     const int wb = __ballot(bad) != 0;
     if (lane == 0) {
       s_lam[wid] = wl;
