@@ -138,9 +138,9 @@ typedef struct {
                        differences), since the collision then returns the equilibrium of U;
                        vklb_get_state rebuilds the populations of the basis. */
   int band_rows;    /* 2D: rows per workgroup band (MHD in the delta bases: at most 64, larger values
-                       are taken as 64); 0 = the default: the tallest power of two from 512 down to
-                       4 rows that gives a step at least 2048 wavefronts (two per SIMD); omega = 1:
-                       the fewest rows, 2 to 16 (MHD 32), that let every wavefront be resident */
+                       are taken as 64); 0 = the default: the fewest rows, 2 to 512, that
+                       let every workgroup of a step be resident at once; omega = 1: 1 to 16 (MHD 32),
+                       by the same rule for its wavefronts */
   int graph_chunk;  /* steps captured per HIP graph (0 = 512; < 0: plain launches) */
   int strip_width;  /* 2D: columns per workgroup (64, 128 or 256); 1D: lanes per workgroup
                        (256 or 512, each finishing W - 2 cells); 0 = tuned default. 2D with omega = 1:

@@ -108,25 +108,29 @@ inline int default_width(int dim, long long nx) {
   if (dim == 1) return 256;
   return nx <= 64 ? 64 : (nx <= 128 ? 128 : 256);
 }
-// Rows per 2D band for strips of `width` columns (width / 64 wavefronts per
-// workgroup): the tallest power of two from 512 down to 4 that still gives the
-// step at least 2048 wavefronts (two per SIMD, the most the MHD march's
-// registers allow). A mid-size grid then does not leave SIMDs idle, and a
-// large one runs its workgroups in one wave with few halo and edge-row reads
-// per cell. Measured on MI355X (FP32, 256-column strips, us per step): 2D
-// Euler 1024^2 33.2 with 8 rows against 56.4 with 32, 512^2 12.5 (4 rows)
-// against 55.2; shallow water 1024^2 26.0 (8) against 45.9; MHD 512^2 37.6
-// (4) against 59.2 (8), 2048^2 309 (32) against 321 (8); Euler 2048^2 and MHD
-// 1024^2 keep 32 and 8. With the rows of whole bands interleaved: Euler
-// 4096^2 472 (128 rows) against 529 (32), 8192^2 2017 (512) against 2082
-// (32); shallow water 4096^2 354 (128) against 389 (32). MHD 1024^2 in
-// 128-column strips: 16-row bands (one wave per SIMD) 126.9 us, 8-row 88.
-inline int default_band(const vklb_grid* g, int width) {
+// Rows per 2D band of the kernels that store populations, for strips of
+// `width` columns: the fewest (from 2 to 512) that let every workgroup be
+// resident at once. A taller band leaves SIMDs idle, a shorter one starts a
+// second round of workgroups that is nearly empty and re-reads more edge rows.
+// Resident are two wavefronts per SIMD in FP32 and for FP64 shallow water and
+// the linear system, one for FP64 Euler and MHD, by the march's registers.
+// (The rule was the tallest power of two that gives 2048 wavefronts: 4 rows
+// for Euler 1001^2, whose 8-row bands make 2016.) Measured on MI355X, us per
+// step, that rule -> this one: FP32 Euler 1001^2 39.4 (4 rows) -> 31.3 (8), 700 x
+// 1300 34.8 (4) -> 27.2 (8), 1024 x 768 25.0 (4) -> 22.9 (6), 300^2 11.7 (4) -> 9.4
+// (2); FP32 MHD 1024 x 768 64.7 (4) -> 55.1 (6), 640 x 900 58.5 (4) -> 49.0 (6);
+// FP64 Euler 640 x 900 57.8 (4) -> 42.6 (11), FP64 MHD 165 (4) -> 132 (11). Unchanged
+// where the sides are powers of two: 2048^2 32 rows, 4096^2 128, 8192^2 512, and
+// 8 for MHD 1024^2.
+inline int default_band(int kind, vklb_precision prec, const vklb_grid* g, int width) {
   const long long strips = (g->n[0] + width - 1) / width, ny = g->dim == 2 ? g->n[1] : 1;
   const long long waves_per_group = (width + 63) / 64;
-  int band = 512;
-  while (band > 4 && strips * ((ny + band - 1) / band) * waves_per_group < 2048) band /= 2;
-  return band;
+  const bool one = prec == VKLB_FP64 && (kind == VKLB_EULER || kind == VKLB_MHD_GLM);
+  const long long resident = (one ? 1024 : 2048) / waves_per_group;  // workgroups
+  long long band = (strips * ny + resident - 1) / resident;
+  band = band < 2 ? 2 : (band > 512 ? 512 : band);
+  while (band < 512 && strips * ((ny + band - 1) / band) > resident) ++band;
+  return int(band);
 }
 // Largest band: the MHD march of the delta bases collides a band's halo cells
 // into LDS for up to 64 rows; the others take any height.
@@ -176,11 +180,16 @@ inline int ustep_grid_of(const vklb_grid* g, int band, bool side) {
 // 512^2 8.7 (1), 7.6 (2), 8.6 (4); 4096^2 150 (16), 171 (32), 166 (64); shallow
 // water 500 x 333 6.4 (1), 6.4 (2), 7.3 (4); MHD 1024^2 70.7 (4), 62.3 (8),
 // 87.7 (16); 2048^2 217 (16), 211 (32), 320 (64); FP64 Euler 1024^2 38.8 (4),
-// 34.3 (8), 38.8 (16); FP64 MHD 512^2 75.1 (2), 60.5 (4), 96.1 (8).
+// 34.3 (8), 38.8 (16); FP64 MHD 512^2 75.1 (2), 60.5 (4), 96.1 (8). Grids of up to
+// 1024 wavefront rows take one row each: Euler 200^2 5.1 (1), 5.7 (2), MHD 9.6
+// (1), 11.9 (2). (Times of the march as first built; it is up to a third faster
+// since, in the same order.)
 inline int default_uband(int kind, vklb_precision prec, const vklb_grid* g) {
   const bool mhd = kind == VKLB_MHD_GLM;
   const long long waves = 1024ll * (prec == VKLB_FP32 ? (mhd ? 2 : 4) : (mhd ? 1 : 2));
-  const long long rows = ((g->n[0] + 63) / 64 * g->n[1] + waves - 1) / waves;
+  const long long lines = (g->n[0] + 63) / 64 * g->n[1];
+  if (lines <= 1024) return 1;  // a row each leaves no SIMD with two wavefronts
+  const long long rows = (lines + waves - 1) / waves;
   const long long most = mhd ? 32 : 16;
   return int(rows < 2 ? 2 : (rows > most ? most : rows));
 }

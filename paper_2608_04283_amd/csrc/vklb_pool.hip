@@ -402,7 +402,7 @@ vklb_status vklb_pool_submit(vklb_pool* p, const vklb_request* rq, uint64_t* tic
   r->cls = class_of(r->sys.kind, r->grid.dim, ust);
   r->band = 32;
   if (r->grid.dim == 2)  // the batched 2D strips are 128 columns, a U solve's 64
-    r->band = ust ? default_uband(r->sys.kind, p->prec, &r->grid) : default_band(&r->grid, 128);
+    r->band = ust ? default_uband(r->sys.kind, p->prec, &r->grid) : default_band(r->sys.kind, p->prec, &r->grid, 128);
   r->halo = default_halo(r->sys.kind);
   if (r->grid.dim == 2) pick_shape(p, r->sys.kind, ust, r->grid.n[0], &r->band, &r->halo);
   r->band = std::min(r->band, ust ? kMaxBand : max_band(r->sys.kind, r->grid.dim, p->basis[r->grid.dim]));

@@ -412,7 +412,7 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
   const bool ust = keeps_u(sys->kind, grid->dim, prec, omega);
   if (ust) pl->K = pl->K.for_ustate();
   int band = o.band_rows;
-  if (band < 1) band = ust ? default_uband(sys->kind, prec, grid) : default_band(grid, width);
+  if (band < 1) band = ust ? default_uband(sys->kind, prec, grid) : default_band(sys->kind, prec, grid, width);
   const int top = ust ? kMaxBand : max_band(sys->kind, grid->dim, pl->basis);
   if (band > top) band = top;
   pl->band = band;
@@ -834,7 +834,7 @@ static vklb_status tune_impl(const vklb_system* sys, vklb_lattice lat, const vkl
       // the default rule's band too, where it is taller than these (large grids)
       std::vector<int> bands = {4, 8, 16, 32, 64};
       const int rule = ust ? default_uband(sys->kind, prec, grid)
-                           : std::min(default_band(grid, w), max_band(sys->kind, 2, resolve_basis(b0.basis, prec, 2)));
+                           : std::min(default_band(sys->kind, prec, grid, w), max_band(sys->kind, 2, resolve_basis(b0.basis, prec, 2)));
       if (rule > 64) bands.push_back(rule);
       for (int band : bands) {
         if (band > 4 && band / 2 >= ny) continue;
