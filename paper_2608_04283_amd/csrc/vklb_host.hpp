@@ -195,11 +195,11 @@ inline int default_uband(int kind, vklb_precision prec, const vklb_grid* g) {
 }
 
 // Lanes of the one-workgroup kernel of a U solve of n cells: as asked
-// (vklb_options.small_grid) where that many can hold the grid, else the fewest
-// of 256, 512 and 1024 that hold it with the fewest cells a lane.
-inline int uwg_lanes(int kind, long long n, int asked) {
-  const int most = kind == VKLB_MHD_GLM ? 1 : (asked == 256 ? 4 : 2);  // cells per lane
-  if ((asked == 256 || asked == 512 || asked == 1024) && n <= (long long)asked * most) return asked;
+// (vklb_options.small_grid) where that is a cell a lane, else the fewest of
+// 256, 512 and 1024 that hold the grid so; above 1024 cells two a lane.
+inline int uwg_lanes(long long n, int asked) {
+  if ((asked == 256 || asked == 512) && n <= asked) return asked;
+  if (asked == 1024) return asked;
   return n <= 256 ? 256 : (n <= 512 ? 512 : 1024);
 }
 
