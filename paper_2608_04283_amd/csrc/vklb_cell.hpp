@@ -768,17 +768,20 @@ struct Equilibrium {
     }
   }
 
-  // The same, and F+ - F- of the axis (what the rest population gives up).
+  // The same for solves that keep U (no stored population to agree with): f+-
+  // as (c U + D / xi) +- F / (2 xi), four operations a value where the form
+  // above takes six, and F+ - F- = 2 D, what the rest population gives up.
   __host__ __device__ static void eval_axis_net(const S* U, const Phys& ph, S ixi, S Lam, S ch, int d, S* fplus,
                                                 S* fminus, S* net) {
-    const S c = S(ph.c);
+    const S c = S(ph.c), hx = S(0.5) * ixi;
     S F[P], D[P];
     C::split(d, U, ph, Lam, ch, F, D);
     for (int v = 0; v < P; ++v) {
-      const S Fp = S(0.5) * F[v] + D[v], Fm = S(0.5) * F[v] - D[v];
-      fplus[v] = c * U[v] + Fp * ixi;
-      fminus[v] = c * U[v] - Fm * ixi;
-      net[v] = Fp - Fm;
+      const S h = hx * F[v];
+      const S s = D[v] * ixi + c * U[v];
+      fplus[v] = s + h;
+      fminus[v] = s - h;
+      net[v] = D[v] + D[v];
     }
   }
 };
