@@ -8,9 +8,10 @@ fused HIP kernel per time step; grids of up to 1024 cells run many steps per
 launch in one workgroup).
 
 Headline workload: 2D Euler four-quadrant Riemann data, 2048^2 cells, 2000
-steps, FP32 populations: the largest single-GPU configuration, and the one
-whose working set (671 MB) is far above the 256 MB Infinity Cache, so its
-HBM fraction measures HBM. The other configurations run beside it under
+steps, FP32: the largest single-GPU configuration. With omega = 1 a solve keeps
+U alone (67 MB a buffer), and its step is bound by the vector unit rather than
+by HBM; the roofline entry states the bytes it cannot do without against the
+HBM peak all the same. The other configurations run beside it under
 "also" (1D shallow water in both lattice forms, 1D Euler shock tube FP32 and
 FP64, the 1D smooth wave to 65,536 cells, 1D and 2D MHD), and the mixed
 request stream under "serving".

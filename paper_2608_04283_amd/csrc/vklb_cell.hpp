@@ -321,8 +321,8 @@ struct Cell<K_EULER, DIM, S> {
     *cfm = S(0);
   }
   __host__ __device__ static bool admissible(const S* U, const Phys& ph) {
-    // p takes in every other field: an infinite or NaN one makes it so
-    return positive_finite(U[0]) && positive_finite(pressure(U, S(ph.gamma)));
+    // (an infinite or NaN momentum leaves p negative or NaN)
+    return positive_finite(U[0]) && pressure(U, S(ph.gamma)) > S(0) && isfinite(U[DIM + 1]);
   }
   __host__ __device__ static void split(int d, const S* U, const Phys& ph, S Lam, S, S* F, S* D) {
     const S gamma = S(ph.gamma);
@@ -480,8 +480,8 @@ struct Cell<K_MHD, DIM, S> {
     *cfm = cm;
   }
   __host__ __device__ static bool admissible(const S* U, const Phys& ph) {
-    // p takes in every other field but psi: an infinite or NaN one makes it so
-    return positive_finite(U[0]) && positive_finite(pressure(U, S(ph.gamma))) && isfinite(U[8]);
+    // (an infinite or NaN momentum or field leaves p negative or NaN)
+    return positive_finite(U[0]) && pressure(U, S(ph.gamma)) > S(0) && isfinite(U[4]) && isfinite(U[8]);
   }
 
   // Primitive-variable wave decomposition along the normal direction.
