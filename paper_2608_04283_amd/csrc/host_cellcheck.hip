@@ -1,7 +1,8 @@
 // Host-side evaluation of the per-cell arithmetic in vklb_cell.hpp, and of
-// the 2D row placement of the population buffers (mem_row, reorder_rows in
-// vklb_host.hpp), for the CPU test suite only (it lets the closed-form splits
-// be compared with the oracle, and the layout be checked, without a GPU).
+// the 2D row placement of the population buffers (mem_row, reorder_rows) and
+// the launch shapes in vklb_host.hpp, for the CPU test suite only (it lets the
+// closed-form splits be compared with the oracle, and layout and shapes be
+// checked, without a GPU).
 // Nothing in the library's entry points calls it.
 #include "vklb_cell.hpp"
 #include "vklb_host.hpp"
@@ -153,5 +154,21 @@ void vklb_cc_reorder_rows(const void* from, void* to, int sx, int ny, int band, 
   L.p = 1;
   L.elem = elem;
   reorder_rows(static_cast<const char*>(from), static_cast<char*>(to), d, L, down_odd != 0, to_grid != 0);
+}
+// Rows a wavefront marches by default in a 2D solve that keeps U, and the
+// wavefronts of a step with `rows` of them. prec: 8 or 4.
+int vklb_cc_default_uband(int kind, int prec, long long nx, long long ny) {
+  vklb_grid g{};
+  g.dim = 2;
+  g.n[0] = nx;
+  g.n[1] = ny;
+  return default_uband(kind, prec == 8 ? VKLB_FP64 : VKLB_FP32, &g);
+}
+long long vklb_cc_ustep_waves(long long nx, long long ny, int rows) {
+  vklb_grid g{};
+  g.dim = 2;
+  g.n[0] = nx;
+  g.n[1] = ny;
+  return ustep_waves(&g, rows);
 }
 }

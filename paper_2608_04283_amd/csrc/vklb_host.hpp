@@ -176,22 +176,29 @@ inline int ustep_grid_of(const vklb_grid* g, int band, bool side) {
 // Euler; more would fit), two in FP64 and for MHD, one for FP64 MHD. At most
 // 16 rows (MHD 32): large grids then take several rounds, whose wavefronts
 // are out of step. Measured on MI355X (FP32, us per step by rows): Euler
-// 2048^2 43.5 (8), 42.8 (16), 47.9 (32); 1024^2 18.3 (2), 14.9 (4), 15.3 (8);
-// 512^2 8.7 (1), 7.6 (2), 8.6 (4); 4096^2 150 (16), 171 (32), 166 (64); shallow
-// water 500 x 333 6.4 (1), 6.4 (2), 7.3 (4); MHD 1024^2 70.7 (4), 62.3 (8),
-// 87.7 (16); 2048^2 217 (16), 211 (32), 320 (64); FP64 Euler 1024^2 38.8 (4),
-// 34.3 (8), 38.8 (16); FP64 MHD 512^2 75.1 (2), 60.5 (4), 96.1 (8). Grids of up to
-// 1024 wavefront rows take one row each: Euler 200^2 5.1 (1), 5.7 (2), MHD 9.6
-// (1), 11.9 (2). (Times of the march as first built; it is up to a third faster
-// since, in the same order.)
+// 2048^2 39.6 (8), 38.0 (16), 41.6 (32); 1024^2 17.0 (2), 13.3 (4), 13.4 (8);
+// 512^2 8.4 (1), 7.0 (2), 7.6 (4); 4096^2 142 (16), 161 (32), 154 (64); 8192^2
+// 507 (16), 541 (32), 557 (64); shallow water 500 x 333 6.3 (1), 6.2 (2), 6.2
+// (3), 6.8 (4); MHD 1024^2 45.7 (4), 40.0 (8), 51.0 (16); 2048^2 136 (16), 132
+// (32), 179 (64); 4096^2 508 (16), 518 (32), 510 (64); FP64 Euler 1024^2 28.0
+// (4), 23.5 (8), 25.8 (16); FP64 MHD 512^2 41.5 (2), 33.2 (4), 50.1 (8). Grids of
+// up to 1024 wavefront rows take one row each: Euler 200^2 5.2 (1), 5.7 (2), MHD
+// 9.6 (1), 12.0 (2). Just above the resident count, and one row more: FP32
+// Euler 1642 x 472, 4108 wavefronts of 4096, 13.1 (3), 11.3 (4); MHD 1199 x 1289,
+// 2052 of 2048, 78.8 (12), 57.9 (13); FP64 Euler 1038 x 961 31.8 (8), 24.8 (9);
+// FP64 MHD 342 x 1532 102 (9), 59.8 (10).
 inline int default_uband(int kind, vklb_precision prec, const vklb_grid* g) {
   const bool mhd = kind == VKLB_MHD_GLM;
   const long long waves = 1024ll * (prec == VKLB_FP32 ? (mhd ? 2 : 4) : (mhd ? 1 : 2));
   const long long lines = (g->n[0] + 63) / 64 * g->n[1];
   if (lines <= 1024) return 1;  // a row each leaves no SIMD with two wavefronts
-  const long long rows = (lines + waves - 1) / waves;
   const long long most = mhd ? 32 : 16;
-  return int(rows < 2 ? 2 : (rows > most ? most : rows));
+  long long rows = (lines + waves - 1) / waves;
+  rows = rows < 2 ? 2 : (rows > most ? most : rows);
+  // a last band that is not full adds wavefronts: one row more where they
+  // would start a second round that is nearly empty
+  while (rows < most && ustep_waves(g, int(rows)) > waves) ++rows;
+  return int(rows);
 }
 
 // Lanes of the one-workgroup kernel of a U solve of n cells: as asked

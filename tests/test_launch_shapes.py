@@ -1,0 +1,43 @@
+"""Launch shapes the library chooses by itself, on the host (no GPU), through the
+host check library, which compiles the functions the library uses."""
+import ctypes
+
+import pytest
+
+from test_cell_math import KIND
+from test_row_layout import CC
+
+
+@pytest.fixture(scope="module")
+def cc():
+    import os
+    if not os.path.exists(CC):
+        from paper_2608_04283_amd import build
+        build.build_cellcheck()
+    L = ctypes.CDLL(CC)
+    ll = ctypes.c_longlong
+    L.vklb_cc_default_uband.argtypes = [ctypes.c_int, ctypes.c_int, ll, ll]
+    L.vklb_cc_ustep_waves.argtypes = [ll, ll, ctypes.c_int]
+    L.vklb_cc_ustep_waves.restype = ll
+    return L
+
+
+SIDES = [1, 2, 3, 63, 64, 65, 128, 200, 258, 300, 333, 500, 580, 724, 819, 1000, 1024, 1199, 1289, 1532, 2048, 4096]
+
+
+@pytest.mark.parametrize("system", ["sw", "euler", "mhd", "linear"])
+@pytest.mark.parametrize("prec", [4, 8])
+def test_default_rows_of_u_solves_are_one_round_of_wavefronts(cc, system, prec):
+    """The fewest rows whose wavefronts are all resident at once, whatever the
+    sides are: at most 16 (MHD 32), one row where a row each is at most 1024."""
+    resident = 1024 * {("mhd", 4): 2, ("mhd", 8): 1}.get((system, prec), 4 if prec == 4 else 2)
+    most = 32 if system == "mhd" else 16
+    for nx in SIDES:
+        for ny in SIDES:
+            rows = cc.vklb_cc_default_uband(KIND[system], prec, nx, ny)
+            waves = [cc.vklb_cc_ustep_waves(nx, ny, r) for r in range(1, most + 1)]
+            if waves[0] <= 1024:
+                want = 1
+            else:
+                want = next((r for r in range(2, most + 1) if waves[r - 1] <= resident), most)
+            assert rows == want, (nx, ny)
