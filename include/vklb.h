@@ -151,7 +151,8 @@ typedef struct {
                        FP32 and 512 in FP64), any boundary condition, run up to 1024 steps per
                        launch in one workgroup, with bitwise the same results as one launch per
                        step: 0 = on, with the fastest lane count measured; 256, 512 or 1024 = on
-                       with that many lanes where they can hold the grid; -1 = off */
+                       with that many lanes (MHD: 256, or with omega = 1 the fewest that hold a cell each
+                       where those asked for do not), of up to 4, 2 or 2 cells each; -1 = off */
   int fold_partials; /* the per-workgroup maxima a step leaves for the next (max |lambda|, max
                        c_f) are read by every workgroup of the next launch; for a step grid of
                        more than this many workgroups a one-workgroup kernel after each launch

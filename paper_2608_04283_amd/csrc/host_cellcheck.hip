@@ -171,4 +171,6 @@ long long vklb_cc_ustep_waves(long long nx, long long ny, int rows) {
   g.n[1] = ny;
   return ustep_waves(&g, rows);
 }
+// Lanes of the one-workgroup kernel of a U solve (vklb_options.small_grid = asked).
+int vklb_cc_uwg_lanes(int kind, long long n, int asked) { return uwg_lanes(kind, n, asked); }
 }

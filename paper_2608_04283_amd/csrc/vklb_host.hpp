@@ -202,12 +202,17 @@ inline int default_uband(int kind, vklb_precision prec, const vklb_grid* g) {
 }
 
 // Lanes of the one-workgroup kernel of a U solve of n cells: as asked
-// (vklb_options.small_grid) where that is a cell a lane, else the fewest of
-// 256, 512 and 1024 that hold the grid so; above 1024 cells two a lane.
-inline int uwg_lanes(long long n, int asked) {
-  if ((asked == 256 || asked == 512) && n <= asked) return asked;
-  if (asked == 1024) return asked;
-  return n <= 256 ? 256 : (n <= 512 ? 512 : 1024);
+// (vklb_options.small_grid) where they hold the grid at up to four (256 lanes)
+// or two cells each (MHD: one); else 256 or 512 lanes of one cell where they
+// hold it so, 512 of two up to 1024 cells and 1024 of two above. Measured (us per
+// step with 256 / 512 / 1024 lanes): FP32 Euler 300 cells 1.61 / 1.14 / 1.37, 700
+// 2.22 / 1.54 / 1.64, 1000 2.75 / 1.87 / 2.11; FP64 Euler 1000 3.77 / 2.95 / 3.22;
+// shallow water 1000 2.14 / 1.48 / 1.74.
+inline int uwg_lanes(int kind, long long n, int asked) {
+  const bool mhd = kind == VKLB_MHD_GLM;
+  const int most = mhd ? 1 : (asked == 256 ? 4 : 2);
+  if ((asked == 256 || asked == 512 || asked == 1024) && n <= (long long)asked * most) return asked;
+  return n <= 256 ? 256 : (n <= (mhd ? 512 : 1024) ? 512 : 1024);
 }
 
 inline int step_grid_of(const vklb_grid* g, int width, int band) {

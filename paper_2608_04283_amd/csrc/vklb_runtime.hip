@@ -527,7 +527,7 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
     int lanes = o.small_grid;
     if (lanes != 256 && lanes != 512 && lanes != 1024) lanes = 512;
     if (sys->kind == VKLB_MHD_GLM) lanes = 256;
-    if (ust) lanes = uwg_lanes(n, o.small_grid);
+    if (ust) lanes = uwg_lanes(sys->kind, n, o.small_grid);
     int cells = int((n + lanes - 1) / lanes);
     if (cells == 3) cells = 4;
     pl->wg_lanes = lanes;

@@ -1,0 +1,23 @@
+"""Launch shapes of solves that keep U (omega = 1): every shape a caller can ask
+for gives the same bits."""
+import numpy as np
+import pytest
+
+from test_gpu_omega1 import populations, run, state1d
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("system,prec", [("sw", "fp32"), ("euler", "fp32"), ("euler", "fp64")])
+@pytest.mark.parametrize("bc", ["periodic", "zero_gradient", "characteristic"])
+def test_one_workgroup_lanes_are_bitwise_the_launch_path(gpu, system, prec, bc):
+    """256 lanes of up to 4 cells, 512 of up to 2 and 1024, with partly filled
+    wavefronts and wavefronts past the end of the grid."""
+    for n in (2, 255, 257, 300, 511, 513, 640, 767, 769, 1000, 1024):
+        P = state1d(system, n, n, bc=(bc, bc))
+        print(f"[case] {system} {n} {prec} {bc}", flush=True)
+        ref = run(gpu, P, prec, 23, small_grid=-1)
+        for lanes in (256, 512, 1024):
+            got = run(gpu, P, prec, 23, small_grid=lanes)
+            assert got[1:3] == ref[1:3] and np.array_equal(got[0], ref[0]), (n, lanes)
+            assert np.array_equal(populations(got[3], P), populations(ref[3], P)), (n, lanes)

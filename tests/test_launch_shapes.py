@@ -19,6 +19,7 @@ def cc():
     L.vklb_cc_default_uband.argtypes = [ctypes.c_int, ctypes.c_int, ll, ll]
     L.vklb_cc_ustep_waves.argtypes = [ll, ll, ctypes.c_int]
     L.vklb_cc_ustep_waves.restype = ll
+    L.vklb_cc_uwg_lanes.argtypes = [ctypes.c_int, ll, ctypes.c_int]
     return L
 
 
@@ -41,3 +42,23 @@ def test_default_rows_of_u_solves_are_one_round_of_wavefronts(cc, system, prec):
             else:
                 want = next((r for r in range(2, most + 1) if waves[r - 1] <= resident), most)
             assert rows == want, (nx, ny)
+
+
+@pytest.mark.parametrize("system", ["sw", "euler", "linear"])
+def test_one_workgroup_lanes_are_the_ones_asked_for(cc, system):
+    """Every grid of up to 1024 cells runs with 256, 512 or 1024 lanes as asked
+    (4, 2 or 1 cells each); without a request with the fastest measured, and
+    larger ones with 1024 of two cells."""
+    for n in list(range(1, 1025, 13)) + [256, 257, 512, 513, 1024]:
+        for lanes in (256, 512, 1024):
+            assert cc.vklb_cc_uwg_lanes(KIND[system], n, lanes) == lanes, n
+        assert cc.vklb_cc_uwg_lanes(KIND[system], n, 0) == (256 if n <= 256 else 512)
+    for n in (1025, 2048):
+        assert [cc.vklb_cc_uwg_lanes(KIND[system], n, k) for k in (0, 256, 512, 1024)] == [1024] * 4
+
+
+def test_one_workgroup_lanes_of_mhd_hold_one_cell_each(cc):
+    for n in (1, 256, 257, 512, 513, 768):
+        for lanes in (0, 256, 512, 1024):
+            got = cc.vklb_cc_uwg_lanes(KIND["mhd"], n, lanes)
+            assert got >= n and got == (lanes if lanes >= n else 256 if n <= 256 else 512 if n <= 512 else 1024)
