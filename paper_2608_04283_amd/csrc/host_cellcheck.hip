@@ -173,4 +173,11 @@ long long vklb_cc_ustep_waves(long long nx, long long ny, int rows) {
 }
 // Lanes of the one-workgroup kernel of a U solve (vklb_options.small_grid = asked).
 int vklb_cc_uwg_lanes(int kind, long long n, int asked) { return uwg_lanes(kind, n, asked); }
+// 1 if the step of a 1D U solve takes tiles of 256 cells.
+int vklb_cc_uside(int kind, int prec, long long n) {
+  vklb_grid g{};
+  g.dim = 1;
+  g.n[0] = n;
+  return uside_of(kind, prec == 8 ? VKLB_FP64 : VKLB_FP32, &g) ? 1 : 0;
+}
 }

@@ -157,12 +157,25 @@ inline bool keeps_u(int kind, int dim, vklb_precision prec, double omega) {
 inline long long ustep_waves(const vklb_grid* g, int band) {
   return ((g->n[0] + 63) / 64) * ((g->n[1] + band - 1) / band);
 }
-// 1D: tiles of 256 cells (a fifth wavefront for the sides) where that takes
-// fewer rounds of one workgroup per compute unit than tiles of 254.
+// 1D: tiles of 256 cells (a fifth wavefront for the sides) where they make a
+// whole number of workgroups per compute unit, of up to `most`, and tiles of
+// 254 make one more on a few units, which the others wait for. Beyond, the
+// units no longer work in step, and the fifth wavefront costs more than the
+// 0.8 % of tiles it saves: from two workgroups a unit on for FP64 MHD (its
+// registers), three for FP32 MHD, eight for the others. us per step with tiles
+// of 254 / 256 on MI355X: Euler FP32 65,536 cells 3.68 / 3.61, 131,072 4.56 / 4.38,
+// 262,144 6.38 / 5.87, 524,288 10.8 / 11.2, 2^20 15.5 / 17.4, 2^24 194 / 236; FP64
+// 65,536 4.18 / 3.94, 262,144 7.27 / 7.19, 2^20 18.5 / 22.3; shallow water FP32
+// 262,144 5.57 / 5.20, 2^20 13.0 / 14.8; MHD FP32 65,536 6.34 / 6.28, 131,072 8.98 /
+// 8.11, 196,608 10.6 / 10.7, 2^20 33.0 / 44.6; MHD FP64 65,536 8.62 / 8.01, 131,072
+// 11.7 / 14.5, 2^20 49.7 / 105. Where both take the same rounds 254 is faster: Euler
+// FP32 16,384 cells 3.26 / 3.49, 98,304 3.94 / 4.23.
 constexpr long long kCUs = 256;
-inline bool uside_of(const vklb_grid* g) {
+inline bool uside_of(int kind, vklb_precision prec, const vklb_grid* g) {
+  if (g->dim != 1) return false;
   const long long a = (g->n[0] + utile1d(true) - 1) / utile1d(true), b = (g->n[0] + utile1d(false) - 1) / utile1d(false);
-  return g->dim == 1 && (a + kCUs - 1) / kCUs < (b + kCUs - 1) / kCUs;
+  const int most = kind != VKLB_MHD_GLM ? 4 : (prec == VKLB_FP32 ? 2 : 1);
+  return a <= most * kCUs && (a + kCUs - 1) / kCUs < (b + kCUs - 1) / kCUs;
 }
 inline int ustep_grid_of(const vklb_grid* g, int band, bool side) {
   if (g->dim == 1) return int((g->n[0] + utile1d(side) - 1) / utile1d(side));
@@ -342,7 +355,8 @@ inline SolveDesc make_desc(char* base, const Layout& L, const vklb_system* sys, 
   d.nfull = grid->dim == 2 && band > 0 ? int(d.ny / band) : 0;
   d.halo = halo;
   d.nblocks = step_grid_of(grid, width, band);
-  if (keeps_u(sys->kind, grid->dim, L.elem == 4 ? VKLB_FP32 : VKLB_FP64, omega)) {
+  const vklb_precision prec = L.elem == 4 ? VKLB_FP32 : VKLB_FP64;
+  if (keeps_u(sys->kind, grid->dim, prec, omega)) {
     // both U buffers in the first population buffer; the second one is the
     // room for a checkpoint's populations, whose rows are in grid order
     const size_t planes = size_t(L.slots > L.Q ? 2 : 1) * L.p;
@@ -351,7 +365,7 @@ inline SolveDesc make_desc(char* base, const Layout& L, const vklb_system* sys, 
     d.pop = d.fb;
     d.fb = base + L.fa_off + planes * size_t(d.us) * d.ny * L.elem;
     d.nfull = 0;
-    d.uside = !batched && uside_of(grid);  // (a batched launch mixes the tiles of many solves)
+    d.uside = !batched && uside_of(sys->kind, prec, grid);  // (a batched launch mixes the tiles of many solves)
     d.nblocks = ustep_grid_of(grid, band, d.uside);
   }
   d.nred = d.nblocks;

@@ -364,13 +364,11 @@ __device__ inline void uadvance1d(const SolveDesc& sd, const typename UKern<KIND
 
 // ---------------------------------------------------------------------------
 // 1D step: one cell per lane, the populations exchanged through LDS. The cells
-// on either side of a tile are collided by the first and the last of its 256 lanes (254 cells a
-// tile), or (SIDE) by a fifth wavefront (256 cells a tile). The fifth
+// on either side of a tile are collided by the first and the last of its 256
+// lanes (254 cells a tile), or (SIDE) by a fifth wavefront (256 cells a tile). The fifth
 // wavefront shares a SIMD with another one, so it pays only where it saves a
-// round of workgroups: 65,536 cells are 256 tiles of 256, one for each compute
-// unit, but 259 of 254, so that three units take two. Euler 65,536 FP64: 4.94
-// us per step with 259 workgroups, 4.09 with 256; MHD 16,384 FP32, 65
-// workgroups or 64, all at once: 5.5 without the fifth wavefront, 6.1 with it.
+// workgroup on some compute units that the others would wait for: 65,536 cells
+// are 256 tiles of 256, one for each unit, but 259 of 254 (uside_of).
 // ---------------------------------------------------------------------------
 constexpr int utile1d(bool side) { return side ? 256 : 254; }
 constexpr int ulanes1d(bool side) { return side ? 320 : 256; }

@@ -517,7 +517,9 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
   // nblocks^2 loads per step (10^12 at a million workgroups), so above the
   // threshold each launch's partials are folded into one entry instead.
   const int fold = o.fold_partials == 0 ? kFoldAbove : o.fold_partials;
-  pl->nred_one = fold > 0 && (ust ? ustep_grid_of(&pl->grid, band, uside_of(&pl->grid)) : step_grid_of(&pl->grid, width, band)) > fold;
+  const int groups = ust ? ustep_grid_of(&pl->grid, band, uside_of(sys->kind, prec, &pl->grid))
+                         : step_grid_of(&pl->grid, width, band);
+  pl->nred_one = fold > 0 && groups > fold;
   // small 1D grids: whole step sequences in one workgroup (bitwise the same)
   pl->wg_cells = pl->wg_lanes = 0;
   if (grid->dim == 1 && o.small_grid >= 0 && pl->K.run_wg && grid->n[0] <= pl->K.wg_max_cells) {

@@ -19,6 +19,7 @@ def cc():
     L.vklb_cc_default_uband.argtypes = [ctypes.c_int, ctypes.c_int, ll, ll]
     L.vklb_cc_ustep_waves.argtypes = [ll, ll, ctypes.c_int]
     L.vklb_cc_ustep_waves.restype = ll
+    L.vklb_cc_uside.argtypes = [ctypes.c_int, ctypes.c_int, ll]
     L.vklb_cc_uwg_lanes.argtypes = [ctypes.c_int, ll, ctypes.c_int]
     return L
 
@@ -62,3 +63,14 @@ def test_one_workgroup_lanes_of_mhd_hold_one_cell_each(cc):
         for lanes in (0, 256, 512, 1024):
             got = cc.vklb_cc_uwg_lanes(KIND["mhd"], n, lanes)
             assert got >= n and got == (lanes if lanes >= n else 256 if n <= 256 else 512 if n <= 512 else 1024)
+
+
+@pytest.mark.parametrize("system,prec,most", [("sw", 4, 4), ("euler", 4, 4), ("euler", 8, 4), ("linear", 8, 4), ("mhd", 4, 2),
+                                              ("mhd", 8, 1)])
+def test_tiles_of_256_only_where_they_save_a_workgroup_a_unit(cc, system, prec, most):
+    """Just below k x 65,536 cells, for the k at which it measured faster, and
+    never above."""
+    ends = [f * k + d for k in range(1, 260) for f in (254 * 256, 65536) for d in (0, 1)]
+    for n in ends + list(range(1, 1 << 25, 9973)):
+        want = any(254 * 256 * k < n <= 65536 * k for k in range(1, most + 1))
+        assert bool(cc.vklb_cc_uside(KIND[system], prec, n)) == want, n
