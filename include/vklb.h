@@ -139,12 +139,13 @@ typedef struct {
                        vklb_get_state rebuilds the populations of the basis. */
   int band_rows;    /* 2D: rows per workgroup band (MHD in the delta bases: at most 64, larger values
                        are taken as 64); 0 = the default: the fewest rows, 2 to 512, that
-                       let every workgroup of a step be resident at once; omega = 1: 1 to 16 (MHD 32),
-                       by the same rule for its wavefronts */
+                       let every workgroup of a step be resident at once. omega = 1: a workgroup's four
+                       wavefronts, 64 columns each, share its band_rows rows of strip_width columns
+                       (256 if 0); 0 = 1 to 16 rows (MHD 32) a wavefront, by the same rule */
   int graph_chunk;  /* steps captured per HIP graph (0 = 512; < 0: plain launches) */
   int strip_width;  /* 2D: columns per workgroup (64, 128 or 256); 1D: lanes per workgroup
                        (256 or 512, each finishing W - 2 cells); 0 = tuned default. 2D with omega = 1:
-                       always 64 columns per wavefront */
+                       see band_rows */
   int halo_rows;    /* 2D: rows of the two halo columns collided per batch (1..32); 0 = tuned default;
                        omega = 1: always 32 */
   int small_grid;   /* 1D grids of up to 1024 cells (256 for MHD; omega = 1: 2048 in FP32, MHD 768 in
@@ -249,7 +250,8 @@ void vklb_destroy(vklb_solver* s);
  *    of up to 1024 cells (not MHD) that run in one workgroup: 256, 512 or 1024
  *    lanes.
  *  - 2D candidates: strips of 64/128/256 columns, bands of 4..64 rows, halo
- *    batches of 2, 8, 16 or 32 rows (omega = 1: bands only).
+ *    batches of 2, 8, 16 or 32 rows (omega = 1: 64-column strips, bands only).
+ *  - The default shape is always among them.
  * All shapes give identical results, so the choice only affects speed. The
  * end condition is ignored while timing. Allocates one workspace
  * (vklb_workspace_bytes) for the duration of the call and synchronizes.
@@ -375,8 +377,8 @@ vklb_status vklb_pool_run(vklb_pool* p, int rounds);
  * count in *n; the rest are kept for the next call) and free their memory. */
 vklb_status vklb_pool_poll(vklb_pool* p, vklb_completion* out, int max, int* n);
 vklb_status vklb_pool_get_stats(const vklb_pool* p, vklb_pool_stats* st);
-/* Tile shapes of the batched 2D kernel (128-column strips; band and halo
- * heights) by the autotuner (vklb_tune over those shapes), once per sample
+/* Tile shapes of the batched 2D kernel (128-column strips; omega = 1: 256 columns,
+ * four rows or more; band and halo heights) by the autotuner (vklb_tune over those shapes), once per sample
  * request: each 2D sample is timed alone for `steps` steps per candidate and
  * its fastest shape is kept for its (system, half-octave size class of n);
  * later admissions take the entry of their class, or the nearest tuned class

@@ -180,4 +180,37 @@ int vklb_cc_uside(int kind, int prec, long long n) {
   g.n[0] = n;
   return uside_of(kind, prec == 8 ? VKLB_FP64 : VKLB_FP32, &g) ? 1 : 0;
 }
+// The autotuner's candidates: (strip_width, band_rows, halo_rows, small_grid) of
+// each into out (room for `room` of them); returns their number.
+int vklb_cc_tune_candidates(int kind, int prec, int dim, long long nx, long long ny, double omega, int pool_2d, int* out,
+                            int room) {
+  vklb_grid g{};
+  g.dim = dim;
+  g.n[0] = nx;
+  g.n[1] = ny;
+  const vklb_options base{};
+  const std::vector<vklb_options> c =
+      tune_candidates(kind, prec == 8 ? VKLB_FP64 : VKLB_FP32, &g, omega, base, pool_2d != 0);
+  for (int i = 0; i < room && i < int(c.size()); ++i) {
+    out[4 * i + 0] = c[i].strip_width;
+    out[4 * i + 1] = c[i].band_rows;
+    out[4 * i + 2] = c[i].halo_rows;
+    out[4 * i + 3] = c[i].small_grid;
+  }
+  return int(c.size());
+}
+// Rows a wavefront of a U solve marches when these options are asked for.
+int vklb_cc_uband_of(int band_rows, int strip_width) { return uband_of(band_rows, strip_width); }
+// Default strip width, band and halo of a 2D solve that stores populations
+// (width 0: the default's; basis 0: the precision's).
+void vklb_cc_default_shape(int kind, int prec, long long nx, long long ny, int width, int* out) {
+  vklb_grid g{};
+  g.dim = 2;
+  g.n[0] = nx;
+  g.n[1] = ny;
+  const vklb_precision p = prec == 8 ? VKLB_FP64 : VKLB_FP32;
+  out[0] = width ? width : default_width(2, nx);
+  out[1] = std::min(default_band(kind, p, &g, out[0]), max_band(kind, 2, resolve_basis(0, p, 2)));
+  out[2] = default_halo(kind);
+}
 }

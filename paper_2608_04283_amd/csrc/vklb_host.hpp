@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <vector>
 
 #include "../../include/vklb.h"
 #include "vklb_launch.hpp"
@@ -214,6 +215,17 @@ inline int default_uband(int kind, vklb_precision prec, const vklb_grid* g) {
   return int(rows);
 }
 
+// Rows a wavefront of a U solve marches: the workgroup's four wavefronts share
+// band_rows rows of strip_width columns (256 if not given), 64 columns each. So
+// the tuner's 64-column strips of 4 to 64 rows are 1 to 16 rows a wavefront, the
+// span default_uband takes its own from.
+constexpr int kUStripWidth = 64 * kUWaves;
+inline int uband_of(int band_rows, int strip_width) {
+  const long long width = strip_width == 64 || strip_width == 128 ? strip_width : kUStripWidth;
+  const long long rows = ((long long)band_rows * width + kUStripWidth - 1) / kUStripWidth;
+  return int(std::min<long long>(rows, kMaxBand));
+}
+
 // Lanes of the one-workgroup kernel of a U solve of n cells: as asked
 // (vklb_options.small_grid) where they hold the grid at up to four (256 lanes)
 // or two cells each (MHD: one); else 256 or 512 lanes of one cell where they
@@ -231,6 +243,62 @@ inline int uwg_lanes(int kind, long long n, int asked) {
 inline int step_grid_of(const vklb_grid* g, int width, int band) {
   if (g->dim == 1) return int((g->n[0] + width - 3) / (width - 2));
   return int(((g->n[0] + width - 1) / width) * ((g->n[1] + band - 1) / band));
+}
+
+// Tile shapes vklb_tune times for a solve with options `base`, its default
+// shape among them. pool_2d: those of the serving pool's batched 2D kernels,
+// in 128-column strips. There a U solve's wavefronts take four rows or more, also
+// where the default is fewer: a sample is timed alone, which favours short
+// bands, but in a full pool the wavefronts of other solves fill the chip and
+// taller bands collide fewer edge rows. Solves/s of 400 mixed requests resident
+// together, by rows of every U solve: 63 (1), 88 (2), 107 (4), 119 (8), 124 (16),
+// 101 by the default rule, 103 by the fastest alone (1 to 5), 115 by these. (A pool
+// of 12 requests is the other way round, ms: 11.2, 11.1, 11.8, 13.9, 18.8.)
+inline std::vector<vklb_options> tune_candidates(int kind, vklb_precision prec, const vklb_grid* g, double omega,
+                                                 const vklb_options& base, bool pool_2d) {
+  std::vector<vklb_options> cand;
+  const bool ust = keeps_u(kind, g->dim, prec, omega);
+  vklb_options o = base;
+  if (g->dim == 1) {
+    // grids that run in one workgroup: its lane count (MHD has one shape)
+    if (g->n[0] <= 1024 && kind != VKLB_MHD_GLM && base.small_grid >= 0) {
+      for (int lanes : {256, 512, 1024}) {
+        o.small_grid = lanes;
+        cand.push_back(o);
+      }
+      return cand;
+    }
+    for (int w : {256, 512}) {
+      if (ust && w > 256) continue;  // one shape
+      o.strip_width = w;
+      cand.push_back(o);
+    }
+    return cand;
+  }
+  const long long nx = g->n[0], ny = g->n[1];
+  for (int w : {64, 128, 256}) {
+    if (ust ? w != (pool_2d ? kUStripWidth : 64)
+            : (pool_2d ? w != 128 : w > 64 && (nx + w - 1) / w * w - nx >= w / 2 && w != default_width(2, nx)))
+      continue;  // (mostly idle lanes)
+    const int rule = ust ? default_uband(kind, prec, g) * (kUStripWidth / w)
+                         : std::min(default_band(kind, prec, g, w), max_band(kind, 2, resolve_basis(base.basis, prec, 2)));
+    std::vector<int> bands = {4, 8, 16, 32, 64};
+    if (std::find(bands.begin(), bands.end(), rule) == bands.end() && !(ust && pool_2d && rule < 4)) bands.push_back(rule);
+    const int usual = ust ? 2 : default_halo(kind);  // (a U solve has one halo batch)
+    for (int band : bands) {
+      const int rows = ust ? uband_of(band, w) : band;
+      if (band > 4 && band != rule && rows / 2 >= ny) continue;
+      for (int halo : {2, 8, 16, 32}) {
+        if (halo > band && !(band == rule && halo == usual)) continue;
+        if (ust && halo != usual) continue;
+        o.strip_width = w;
+        o.band_rows = band;
+        o.halo_rows = halo;
+        cand.push_back(o);
+      }
+    }
+  }
+  return cand;
 }
 
 // Argument checks of vklb_create (Sec. 2.3 omega range, Sec. 3.2 CFL number,

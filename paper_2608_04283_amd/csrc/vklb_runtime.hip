@@ -506,9 +506,12 @@ vklb_status plan_solve(const vklb_system* sys, vklb_lattice lat, const vklb_grid
   const bool ust = keeps_u(sys->kind, grid->dim, prec, omega);
   if (ust) pl->K = pl->K.for_ustate();
   int band = o.band_rows;
-  if (band < 1) band = ust ? default_uband(sys->kind, prec, grid) : default_band(sys->kind, prec, grid, width);
-  const int top = ust ? kMaxBand : max_band(sys->kind, grid->dim, pl->basis);
-  if (band > top) band = top;
+  if (ust) {
+    band = band < 1 ? default_uband(sys->kind, prec, grid) : uband_of(band, o.strip_width);
+  } else {
+    if (band < 1) band = default_band(sys->kind, prec, grid, width);
+    band = std::min(band, max_band(sys->kind, grid->dim, pl->basis));
+  }
   pl->band = band;
   int halo = o.halo_rows;
   if (halo < 1 || halo > 32) halo = default_halo(sys->kind);
@@ -876,8 +879,7 @@ vklb_status vklb_set_state(vklb_solver* s, const void* host) {
 }  // extern "C"
 
 // vklb_tune over the shapes of a single solve, or (pool_2d) over the band and
-// halo heights of the serving pool's batched 2D kernel, whose strips are 128
-// columns wide.
+// halo heights of the serving pool's batched 2D kernels.
 static vklb_status tune_impl(const vklb_system* sys, vklb_lattice lat, const vklb_grid* grid, const vklb_speed* lambda,
                              double omega, const vklb_bc bc[2], const vklb_equilibrium* eq, vklb_precision prec,
                              const vklb_options* base, const double* U0_host, int steps, void* hip_stream,
@@ -890,62 +892,7 @@ static vklb_status tune_impl(const vklb_system* sys, vklb_lattice lat, const vkl
   vklb_options b0;
   if (base) b0 = *base;
   else memset(&b0, 0, sizeof b0);
-  // candidate tile shapes
-  std::vector<vklb_options> cand;
-  // a solve that keeps U has one strip width and one halo batch
-  const bool ust = keeps_u(sys->kind, grid->dim, prec, omega);
-  if (pool_2d) {
-    const long long ny = grid->n[1];
-    for (int band : {4, 8, 16, 32, 64}) {
-      if (band > 4 && band / 2 >= ny) continue;
-      for (int halo : {2, 8, 16, 32}) {
-        if (halo > band || (ust && halo > 2)) continue;
-        vklb_options o = b0;
-        o.strip_width = 128;
-        o.band_rows = band;
-        o.halo_rows = halo;
-        cand.push_back(o);
-      }
-    }
-  } else if (grid->dim == 1) {
-    for (int w : {256, 512}) {
-      if (ust && w > 256) continue;
-      vklb_options o = b0;
-      o.strip_width = w;
-      cand.push_back(o);
-    }
-    // grids that run in one workgroup: its lane count (MHD has one shape)
-    if (grid->n[0] <= 1024 && sys->kind != VKLB_MHD_GLM && b0.small_grid >= 0) {
-      cand.clear();
-      for (int lanes : {256, 512, 1024}) {
-        vklb_options o = b0;
-        o.small_grid = lanes;
-        cand.push_back(o);
-      }
-    }
-  } else {
-    const long long nx = grid->n[0], ny = grid->n[1];
-    for (int w : {64, 128, 256}) {
-      if (ust && w > 64) continue;
-      if (w > 64 && (nx + w - 1) / w * w - nx >= w / 2) continue;  // mostly idle lanes
-      // the default rule's band too, where it is taller than these (large grids)
-      std::vector<int> bands = {4, 8, 16, 32, 64};
-      const int rule = ust ? default_uband(sys->kind, prec, grid)
-                           : std::min(default_band(sys->kind, prec, grid, w), max_band(sys->kind, 2, resolve_basis(b0.basis, prec, 2)));
-      if (rule > 64) bands.push_back(rule);
-      for (int band : bands) {
-        if (band > 4 && band / 2 >= ny) continue;
-        for (int halo : {2, 8, 16, 32}) {
-          if (halo > band || (ust && halo > 2)) continue;
-          vklb_options o = b0;
-          o.strip_width = w;
-          o.band_rows = band;
-          o.halo_rows = halo;
-          cand.push_back(o);
-        }
-      }
-    }
-  }
+  const std::vector<vklb_options> cand = tune_candidates(sys->kind, prec, grid, omega, b0, pool_2d);
   const size_t bytes = vklb_workspace_bytes(sys, lat, grid, prec);
   void* buf = nullptr;
   hipError_t e = hipMalloc(&buf, bytes);

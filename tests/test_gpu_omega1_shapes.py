@@ -3,7 +3,7 @@ for gives the same bits."""
 import numpy as np
 import pytest
 
-from test_gpu_omega1 import populations, run, state1d
+from test_gpu_omega1 import populations, run, state1d, state2d
 
 pytestmark = pytest.mark.gpu
 
@@ -21,3 +21,15 @@ def test_one_workgroup_lanes_are_bitwise_the_launch_path(gpu, system, prec, bc):
             got = run(gpu, P, prec, 23, small_grid=lanes)
             assert got[1:3] == ref[1:3] and np.array_equal(got[0], ref[0]), (n, lanes)
             assert np.array_equal(populations(got[3], P), populations(ref[3], P)), (n, lanes)
+
+
+@pytest.mark.parametrize("system,prec", [("sw", "fp32"), ("euler", "fp32"), ("mhd", "fp32"), ("mhd", "fp64")])
+def test_rows_and_strips_give_identical_results(gpu, system, prec):
+    """1 to 45 rows a wavefront (more than one batch of halo rows, a last band
+    that is not full), asked for as rows of 64, 128 or 256 columns."""
+    P = state2d(system, 200, 90, 5, bc=("zero_gradient", "periodic"))
+    ref = run(gpu, P, prec, 12)
+    for width, rows in ((64, 4), (64, 12), (64, 180), (128, 5), (128, 66), (256, 7), (256, 33), (0, 45)):
+        got = run(gpu, P, prec, 12, strip_width=width, band_rows=rows)
+        assert got[1:3] == ref[1:3] and np.array_equal(got[0], ref[0]), (width, rows)
+        assert np.array_equal(populations(got[3], P), populations(ref[3], P)), (width, rows)

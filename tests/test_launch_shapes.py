@@ -20,6 +20,11 @@ def cc():
     L.vklb_cc_ustep_waves.argtypes = [ll, ll, ctypes.c_int]
     L.vklb_cc_ustep_waves.restype = ll
     L.vklb_cc_uside.argtypes = [ctypes.c_int, ctypes.c_int, ll]
+    L.vklb_cc_tune_candidates.argtypes = [ctypes.c_int] * 3 + [ll, ll, ctypes.c_double, ctypes.c_int, ctypes.c_void_p,
+                                                               ctypes.c_int]
+    L.vklb_cc_uband_of.argtypes = [ctypes.c_int, ctypes.c_int]
+    L.vklb_cc_default_shape.argtypes = [ctypes.c_int, ctypes.c_int, ll, ll, ctypes.c_int, ctypes.c_void_p]
+    L.vklb_cc_default_shape.restype = None
     L.vklb_cc_uwg_lanes.argtypes = [ctypes.c_int, ll, ctypes.c_int]
     return L
 
@@ -74,3 +79,48 @@ def test_tiles_of_256_only_where_they_save_a_workgroup_a_unit(cc, system, prec, 
     for n in ends + list(range(1, 1 << 25, 9973)):
         want = any(254 * 256 * k < n <= 65536 * k for k in range(1, most + 1))
         assert bool(cc.vklb_cc_uside(KIND[system], prec, n)) == want, n
+
+
+def candidates(cc, system, prec, nx, ny=0, omega=1.0, pool=False):
+    out = (ctypes.c_int * 800)()
+    n = cc.vklb_cc_tune_candidates(KIND[system], prec, 2 if ny else 1, nx, max(ny, 1), omega, int(pool), out, 200)
+    assert 0 < n <= 200
+    c = [tuple(out[4 * i:4 * i + 4]) for i in range(n)]
+    assert len(set(c)) == n
+    return c
+
+
+@pytest.mark.parametrize("pool", [False, True])
+@pytest.mark.parametrize("omega", [1.0, 1.5])
+@pytest.mark.parametrize("prec", [4, 8])
+@pytest.mark.parametrize("system", ["sw", "euler", "mhd", "linear"])
+def test_the_tuner_times_the_default_2d_shape(cc, system, prec, omega, pool):
+    for nx in SIDES + [129, 257, 8192]:
+        for ny in SIDES:
+            c = candidates(cc, system, prec, nx, ny, omega, pool)
+            if omega == 1.0:
+                rows = [cc.vklb_cc_uband_of(b, w) for w, b, _, _ in c]
+                rule = cc.vklb_cc_default_uband(KIND[system], prec, nx, ny)
+                assert len(set(rows)) == len(rows) and (rule in rows or pool and rule < 4)
+                assert not pool or min(rows) == 4  # (a full pool runs taller bands faster)
+            else:
+                d = (ctypes.c_int * 3)()
+                cc.vklb_cc_default_shape(KIND[system], prec, nx, ny, 128 if pool else 0, d)
+                assert tuple(d) + (0,) in c, (nx, ny)
+
+
+def test_rows_of_a_wavefront_of_a_u_solve(cc):
+    """A workgroup's four wavefronts share band_rows rows of strip_width columns."""
+    for band, width, rows in ((1, 0, 1), (40, 0, 40), (40, 256, 40), (40, 77, 40), (40, 128, 20), (5, 128, 3),
+                              (4, 64, 1), (5, 64, 2), (64, 64, 16), (3, 64, 1), (2**31 - 1, 64, 4096), (5000, 0, 4096)):
+        assert cc.vklb_cc_uband_of(band, width) == rows
+
+
+@pytest.mark.parametrize("omega", [1.0, 1.5])
+def test_the_tuner_times_each_1d_shape_once(cc, omega):
+    for n in (1, 200, 256, 257, 513, 1024):
+        lanes = [c[3] for c in candidates(cc, "euler", 4, n, omega=omega)]
+        assert lanes == [256, 512, 1024]
+        assert [cc.vklb_cc_uwg_lanes(KIND["euler"], n, k) for k in lanes] == lanes
+        assert cc.vklb_cc_uwg_lanes(KIND["euler"], n, 0) in lanes
+    assert [c[0] for c in candidates(cc, "euler", 4, 3000, omega=omega)] == ([256] if omega == 1.0 else [256, 512])
