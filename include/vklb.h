@@ -213,7 +213,11 @@ vklb_status vklb_init_device(vklb_solver* s, const double* U0_device);
 vklb_status vklb_step(vklb_solver* s, int64_t n);
 
 /* Copy U = sum_q f_q to U_host (FP64 SoA [p][cells]); t and steps may be NULL.
- * Synchronizes; returns VKLB_ERR_NONPHYSICAL if such a state was produced. */
+ * Synchronizes; returns VKLB_ERR_NONPHYSICAL if such a state was produced.
+ * Here and in vklb_get_state, a copy of 8 MiB or more to pageable memory goes
+ * through up to four host threads, which end before the call returns, and
+ * 8 MiB of pinned host memory, which the first such copy allocates and
+ * vklb_destroy frees; a host that refuses either gets a plain copy. */
 vklb_status vklb_moments(vklb_solver* s, double* U_host, double* t, int64_t* steps);
 
 /* Time, step count and whether the end condition has been reached (no more

@@ -7,14 +7,13 @@
 #include <string.h>
 
 #include <algorithm>
-#include <atomic>
 #include <mutex>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "../../include/vklb.h"
 #include "vklb_host.hpp"
+#include "vklb_hostcopy.hpp"
 
 using namespace vklb;
 
@@ -189,8 +188,7 @@ struct vklb_solver {
   hipGraphExec_t gexec = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   bool timed = false;
-  char* pin = nullptr;      // pinned staging of large copies to the host (kPinSlots chunks), made when first needed
-  hipEvent_t pin_ev[8] = {};
+  HostCopyRing ring;        // large copies to the host
   std::string err;
   int device = 0;
   int basis = 0;
@@ -357,93 +355,9 @@ vklb_status read_view(vklb_solver* s, HostView* v) {
   return VKLB_OK;
 }
 
-// Copy `bytes` of device memory to pageable host memory, in stream order, and
-// wait for it. Large copies go through pinned chunks: the device copies into
-// a ring of them while worker threads move finished chunks on, so the copy
-// engine, the page faults of a fresh destination and the host copy overlap.
-// hipMemcpyAsync to pageable memory does these one after another, at 9-10 GB/s
-// (the fields of Euler 2048^2, 134 MB: 14.5 ms), against 56 GB/s of a pinned
-// copy and 14 GB/s a thread of a copy into fresh pages. Small copies, and
-// hosts that give no threads or pinned memory, take that call.
-constexpr size_t kPinChunk = size_t(1) << 20;
-constexpr int kPinSlots = 8, kPinWorkers = 4;
-constexpr size_t kPinAbove = size_t(8) << 20;
-
-bool make_pin(vklb_solver* s) {
-  if (s->pin) return true;
-  for (int i = 0; i < kPinSlots; ++i)
-    if (!s->pin_ev[i] && hipEventCreateWithFlags(&s->pin_ev[i], hipEventDisableTiming) != hipSuccess) return false;
-  void* p = nullptr;
-  if (hipHostMalloc(&p, kPinChunk * kPinSlots, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  s->pin = static_cast<char*>(p);
-  return true;
-}
-
+// Copy `bytes` of device memory to host memory in stream order, and wait for it.
 vklb_status copy_to_host(vklb_solver* s, void* dst, const void* src, size_t bytes) {
-  bool pinned = false;  // a pinned destination is copied to directly
-  if (bytes >= kPinAbove) {
-    hipPointerAttribute_t at;
-    if (hipPointerGetAttributes(&at, dst) == hipSuccess) pinned = at.type != hipMemoryTypeUnregistered;
-    else (void)hipGetLastError();
-  }
-  const int cpus = int(std::thread::hardware_concurrency());
-  const int workers = std::min(kPinWorkers, cpus - 1);
-  if (bytes < kPinAbove || pinned || workers < 2 || !make_pin(s)) {
-    HIPCHK(s, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    return VKLB_OK;
-  }
-  const long long chunks = (long long)((bytes + kPinChunk - 1) / kPinChunk);
-  std::atomic<long long> issued{0};       // chunks handed to the device
-  std::atomic<long long> moved[kPinSlots];  // per slot: chunks moved on
-  std::atomic<int> failed{int(hipSuccess)};
-  for (auto& m : moved) m.store(0);
-  auto work = [&](int w) {
-    for (long long i = w; i < chunks; i += workers) {
-      while (issued.load(std::memory_order_acquire) <= i) {
-        if (failed.load() != int(hipSuccess)) return;
-        std::this_thread::yield();
-      }
-      const int slot = int(i % kPinSlots);
-      const hipError_t e = hipEventSynchronize(s->pin_ev[slot]);
-      if (e != hipSuccess) {
-        failed.store(int(e));
-        return;
-      }
-      const size_t off = size_t(i) * kPinChunk;
-      memcpy(static_cast<char*>(dst) + off, s->pin + size_t(slot) * kPinChunk, std::min(kPinChunk, bytes - off));
-      moved[slot].fetch_add(1, std::memory_order_release);
-    }
-  };
-  std::vector<std::thread> pool;
-  try {
-    for (int w = 0; w < workers; ++w) pool.emplace_back(work, w);
-  } catch (...) {  // no threads to be had: nothing was issued yet
-    failed.store(int(hipErrorUnknown));
-    for (std::thread& t : pool) t.join();
-    HIPCHK(s, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    return VKLB_OK;
-  }
-  for (long long i = 0; i < chunks && failed.load() == int(hipSuccess); ++i) {
-    const int slot = int(i % kPinSlots);
-    while (moved[slot].load(std::memory_order_acquire) < i / kPinSlots && failed.load() == int(hipSuccess))
-      std::this_thread::yield();
-    const size_t off = size_t(i) * kPinChunk;
-    hipError_t e = hipMemcpyAsync(s->pin + size_t(slot) * kPinChunk, static_cast<const char*>(src) + off,
-                                  std::min(kPinChunk, bytes - off), hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess) e = hipEventRecord(s->pin_ev[slot], s->stream);
-    if (e != hipSuccess) failed.store(int(e));
-    else issued.store(i + 1, std::memory_order_release);
-  }
-  for (std::thread& t : pool) t.join();
-  if (failed.load() != int(hipSuccess)) {
-    (void)hipStreamSynchronize(s->stream);  // no copy into the ring is left in flight
-    return hip_fail(s, hipError_t(failed.load()), "copy to the host");
-  }
+  HIPCHK(s, s->ring.copy(dst, src, bytes, s->stream, s->device));
   return VKLB_OK;
 }
 
@@ -962,9 +876,7 @@ void vklb_destroy(vklb_solver* s) {
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   if (s->ev0) (void)hipEventDestroy(s->ev0);
   if (s->ev1) (void)hipEventDestroy(s->ev1);
-  for (hipEvent_t e : s->pin_ev)
-    if (e) (void)hipEventDestroy(e);
-  if (s->pin) (void)hipHostFree(s->pin);
+  s->ring.release();
   if (s->own_buf && s->buf) (void)hipFree(s->buf);
   delete s;
 }
