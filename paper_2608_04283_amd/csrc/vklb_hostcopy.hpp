@@ -30,7 +30,9 @@ class HostCopyRing {
   static constexpr int kSlots = 8, kWorkers = 4;
   static constexpr size_t kAbove = size_t(8) << 20;  // smaller copies: one call
 
-  // Copies in the order of `stream` (of `device`) and waits for the copy.
+  // Copies in the order of `stream` (of `device`); the copy is complete when the
+  // stream is. (It is not waited for here: a caller that reads more behind it
+  // would wait twice, 20 us of the 65 that a small grid's moments take.)
   hipError_t copy(void* dst, const void* src, size_t bytes, hipStream_t stream, int device) {
     const int workers = std::min<int>(kWorkers, int(std::thread::hardware_concurrency()) - 1);
     if (bytes >= kAbove && workers >= 2 && !is_pinned(dst) && make()) {
@@ -38,8 +40,7 @@ class HostCopyRing {
       const hipError_t r = through_ring(dst, src, bytes, stream, device, workers, &started);
       if (started) return r;
     }
-    const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, stream);
-    return e == hipSuccess ? hipStreamSynchronize(stream) : e;
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, stream);
   }
 
   void release() {

@@ -52,6 +52,7 @@ struct DevState {
   long long max_steps;
   unsigned long long err_word;    // min over detections of (step << 32 | cell); ~0 if none
   double last[3];                 // xi, Lambda, c_h of the last step taken (or of the initialization)
+  long long pop_n;                // step whose populations SolveDesc::pop was given (-1: none)
 };
 
 // Everything a kernel needs to know about one solve (passed by value).

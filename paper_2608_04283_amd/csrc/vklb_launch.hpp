@@ -25,8 +25,7 @@ struct Launchers {
   launch_fn ustep = nullptr;
   launch_fn uinit = nullptr;
   launch_fn umoments = nullptr;
-  launch_fn upopulate = nullptr;        // populations of the current step, after at least one step
-  launch_fn upopulate_first = nullptr;  // and before the first one
+  launch_fn upopulate = nullptr;  // populations of the current step
   launch_fn uextract = nullptr;
   batched_fn ubatched = nullptr;
   wg_fn urun_wg = nullptr;

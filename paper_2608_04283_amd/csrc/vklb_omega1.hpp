@@ -734,16 +734,22 @@ __global__ void __launch_bounds__(256) k_umoments(const SolveDesc sd) {
 }
 
 // Populations of the current step n into sd.pop, in the blocked layout of the
-// kernels that store them, bit for bit what those would hold: after a step,
-// f_q(x) = f^eq_q(U^{n-1}(x - v_q)) with that step's speeds; before the
-// first one (first = 1), f^eq(U_0) of the cell itself.
+// kernels that store them: after a step, f_q(x) = f^eq_q(U^{n-1}(x - v_q)) with
+// that step's speeds; before the first one, f^eq(U_0) of the cell itself. They
+// are this solve's own: in the sum form they add up, bit for bit, to the U it
+// holds, and they equal the populations a storing kernel would hold up to
+// rounding (its equilibria are formed in another order, eval_axis). Those an
+// initialization or a restored checkpoint left there are kept (pop_n; n never
+// comes back to it without another of the two).
 template <int KIND, int DIM, class T, int BASIS>
-__global__ void __launch_bounds__(256) k_upopulate(const SolveDesc sd, int first) {
+__global__ void __launch_bounds__(256) k_upopulate(const SolveDesc sd) {
   using UK = UKern<KIND, DIM, T, BASIS>;
   using K = typename UK::K;
   constexpr int P = UK::P, Q = UK::Q, REST = UK::REST;
   const DevState* st = sd.st;
   const long long n = st->S[sd.par].n;
+  if (n == st->pop_n) return;
+  const bool first = n == 0;
   const T* __restrict__ cur = (const T*)((n & 1) ? sd.fb : sd.fa);
   const T* __restrict__ old = first ? cur : (const T*)((n & 1) ? sd.fa : sd.fb);
   T* __restrict__ f = (T*)sd.pop;

@@ -193,7 +193,6 @@ struct vklb_solver {
   int device = 0;
   int basis = 0;
   long long launches = 0;   // step launches since init (selects the parity)
-  long long pop_n = -1;     // U solves: step whose populations sd.pop holds (-1: none)
   int wg_cells = 0;         // > 0: 1D steps run in one workgroup, this many cells per lane
   int wg_lanes = 0;         // and this many lanes
 };
@@ -235,7 +234,8 @@ static vklb_status set_npar(vklb_solver* s, int npar) {
   return VKLB_OK;
 }
 
-vklb_status reset_state(vklb_solver* s, double t, long long n, int done) {
+// pop_n: U solves, the step whose populations sd.pop holds (-1: none).
+vklb_status reset_state(vklb_solver* s, double t, long long n, int done, long long pop_n) {
   vklb_status st = set_npar(s, int(n & 1));
   if (st != VKLB_OK) return st;
   DevState h;
@@ -247,6 +247,7 @@ vklb_status reset_state(vklb_solver* s, double t, long long n, int done) {
   h.T = s->T;
   h.max_steps = s->max_steps;
   h.err_word = ~0ull;
+  h.pop_n = pop_n;
   HIPCHK(s, hipMemcpyAsync(s->buf + s->L.state_off, &h, sizeof(h), hipMemcpyHostToDevice, s->stream));
   s->launches = 0;
   return VKLB_OK;
@@ -355,7 +356,7 @@ vklb_status read_view(vklb_solver* s, HostView* v) {
   return VKLB_OK;
 }
 
-// Copy `bytes` of device memory to host memory in stream order, and wait for it.
+// Copy `bytes` of device memory to host memory; complete when the stream is.
 vklb_status copy_to_host(vklb_solver* s, void* dst, const void* src, size_t bytes) {
   HIPCHK(s, s->ring.copy(dst, src, bytes, s->stream, s->device));
   return VKLB_OK;
@@ -559,7 +560,8 @@ static vklb_status init_from(vklb_solver* s, const double* U0, hipMemcpyKind kin
   HIPCHK(s, hipSetDevice(s->device));
   const long long cells = (long long)s->sd.nx * s->sd.ny;
   HIPCHK(s, hipMemcpyAsync(const_cast<double*>(s->sd.stage), U0, size_t(s->L.p) * cells * 8, kind, s->stream));
-  vklb_status st = reset_state(s, 0.0, 0, 0);
+  // the sum form keeps the populations it starts from
+  vklb_status st = reset_state(s, 0.0, 0, 0, s->sd.ustate && s->basis == 0 ? 0 : -1);
   if (st != VKLB_OK) return st;
   SolveDesc d = s->sd;
   d.par = 0;
@@ -567,7 +569,6 @@ static vklb_status init_from(vklb_solver* s, const double* U0, hipMemcpyKind kin
   st = fold_partials(s, s->stream, 0);
   if (st != VKLB_OK) return st;
   HIPCHK(s, s->K.init_feq(d, grid_for_cells(cells), s->stream));
-  s->pop_n = s->sd.ustate && s->basis == 0 ? 0 : -1;  // the sum form keeps the populations it starts from
   s->inited = true;
   return VKLB_OK;
 }
@@ -718,23 +719,23 @@ vklb_status vklb_get_state(vklb_solver* s, void* host, double* t, int64_t* steps
   if (!s || !host) return VKLB_ERR_ARG;
   if (!s->inited) return fail(s, VKLB_ERR_STATE, "vklb_get_state before vklb_init");
   HIPCHK(s, hipSetDevice(s->device));
-  HostView v;
-  vklb_status st = read_view(s, &v);
-  if (st != VKLB_OK) return st;
   const size_t pop = vklb_state_bytes(s) - sizeof(CkptTrailer);
-  const char* src = (v.S.n & 1) ? static_cast<const char*>(s->sd.fb) : static_cast<const char*>(s->sd.fa);
-  if (s->sd.ustate) {
-    src = static_cast<const char*>(s->sd.pop);
-    if (s->pop_n != v.S.n) {
-      SolveDesc d = s->sd;
-      d.par = int(s->launches & 1);
-      const int grid = grid_for_cells((long long)d.nx * d.ny);
-      HIPCHK(s, v.S.n == 0 ? s->K.upopulate_first(d, grid, s->stream) : s->K.upopulate(d, grid, s->stream));
-      s->pop_n = v.S.n;
-    }
+  HostView v;
+  vklb_status st;
+  if (s->sd.ustate) {  // populations, copy and scalars in one wait
+    SolveDesc d = s->sd;
+    d.par = int(s->launches & 1);
+    HIPCHK(s, s->K.upopulate(d, grid_for_cells((long long)d.nx * d.ny), s->stream));
+    st = copy_to_host(s, host, s->sd.pop, pop);
+    if (st == VKLB_OK) st = read_view(s, &v);
+    if (st != VKLB_OK) return st;
+  } else {
+    st = read_view(s, &v);
+    if (st != VKLB_OK) return st;
+    st = copy_to_host(s, host, (v.S.n & 1) ? s->sd.fb : s->sd.fa, pop);
+    if (st != VKLB_OK) return st;
+    HIPCHK(s, hipStreamSynchronize(s->stream));
   }
-  st = copy_to_host(s, host, src, pop);
-  if (st != VKLB_OK) return st;
   if (s->sd.nfull > 1) {  // rows to grid order
     std::vector<char> dev(static_cast<const char*>(host), static_cast<const char*>(host) + pop);
     reorder_rows(dev.data(), static_cast<char*>(host), s->sd, s->L, s->sys.kind == VKLB_MHD_GLM, true);
@@ -771,19 +772,17 @@ vklb_status vklb_set_state(vklb_solver* s, const void* host) {
   } else {
     HIPCHK(s, hipMemcpyAsync(dst, host, pop, hipMemcpyHostToDevice, s->stream));
   }
-  vklb_status st = reset_state(s, tr.t, tr.n, tr.done);
+  vklb_status st = reset_state(s, tr.t, tr.n, tr.done, tr.n);
   if (st != VKLB_OK) return st;
   // The saved maxima stand in for the partials of parity 0 (the max is exact).
   std::vector<double> part(size_t(2) * s->sd.nblocks, 0.0);
   part[0] = tr.lam7;
   part[s->sd.nblocks] = tr.cfm;
   HIPCHK(s, hipMemcpyAsync(s->sd.part, part.data(), part.size() * 8, hipMemcpyHostToDevice, s->stream));
-  s->pop_n = -1;
   if (s->sd.ustate) {
     SolveDesc d = s->sd;
     d.par = 0;
     HIPCHK(s, s->K.uextract(d, grid_for_cells((long long)d.nx * d.ny), s->stream));
-    s->pop_n = tr.n;
   }
   HIPCHK(s, hipStreamSynchronize(s->stream));
   s->inited = true;

@@ -124,6 +124,8 @@ static hipError_t copy(vklb::HostCopyRing& ring, size_t bytes, const char* what)
   unsigned x = unsigned(bytes) * 2654435761u + 1;
   for (auto& c : src) c = (unsigned char)((x = x * 1664525u + 1013904223u) >> 24);
   const hipError_t e = ring.copy(dst.data(), src.data(), bytes, nullptr, 0);
+  if (bytes >= vklb::HostCopyRing::kAbove && g_buffers) CHECK(g_queue.empty());
+  (void)hipStreamSynchronize(nullptr);
   CHECK(g_queue.empty());  // nothing in flight, whatever happened
   if (e == hipSuccess) CHECK(memcmp(src.data(), dst.data(), bytes) == 0);
   for (int i = 0; i < 16; ++i) CHECK(dst[bytes + i] == 0xee);

@@ -33,3 +33,41 @@ def test_rows_and_strips_give_identical_results(gpu, system, prec):
         got = run(gpu, P, prec, 12, strip_width=width, band_rows=rows)
         assert got[1:3] == ref[1:3] and np.array_equal(got[0], ref[0]), (width, rows)
         assert np.array_equal(populations(got[3], P), populations(ref[3], P)), (width, rows)
+
+
+@pytest.mark.parametrize("prec,basis", [("fp64", 0), ("fp32", 2), ("fp32", 3)])
+def test_checkpoints_follow_the_state(gpu, prec, basis):
+    """The populations of a checkpoint are the current state's, whatever was
+    rebuilt, initialized or restored before: asked for twice, at the same step
+    count of another initial state, and before the first step after others."""
+    A, B = (state2d("euler", 70, 20, seed, bc=("periodic", "periodic")) for seed in (1, 2))
+    ref = {(k, n): populations(run(gpu, P, prec, n, basis=basis)[3], P) for k, P in (("a", A), ("b", B)) for n in (0, 4, 7)}
+    s = gpu.Solver(A, precision=prec, basis=basis)
+    dt = np.float32 if prec == "fp32" else np.float64
+
+    def check(key):
+        for _ in range(2):
+            blob = s.get_state()[0]
+            assert np.array_equal(populations(blob[:-128].view(dt), A), ref[key]), key
+        return blob
+
+    s.init(A.U0)
+    check(("a", 0))
+    s.step(4)
+    a4 = check(("a", 4))
+    s.step(3)
+    check(("a", 7))
+    s.init(B.U0)
+    s.step(4)
+    check(("b", 4))
+    s.init(A.U0)
+    check(("a", 0))
+    s.init(B.U0)
+    s.step(7)
+    s.set_state(a4)
+    check(("a", 4))
+    s.step(3)
+    check(("a", 7))
+    s.init(B.U0)
+    check(("b", 0))
+    s.close()
