@@ -42,6 +42,7 @@ for _p in (ROOT, os.path.join(ROOT, "tests")):
         sys.path.insert(0, _p)
 
 from paper_2608_04283_amd import inputs as I  # noqa: E402
+from paper_2608_04283_amd.serving import alg_bytes, keeps_u  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
 
@@ -64,19 +65,6 @@ HEADLINE = "euler2d_quadrants"
 def log(msg):
     """Progress of the run, on stderr (the JSON line alone goes to stdout)."""
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
-
-
-def keeps_u(P, prec):
-    """The library's rule for the solves that store U alone."""
-    return P.omega == 1.0 and not (P.system == "sw" and P.dim == 1 and prec == "fp64")
-
-
-def alg_bytes_per_cell_step(P, prec):
-    """Bytes a cell-step cannot do without: the stored state read once and
-    written once. Solves with omega = 1 store U (the collision then returns the
-    equilibrium of U), the others every population (see keeps_u)."""
-    slots = 1 if keeps_u(P, prec) else P.Q
-    return 2 * slots * P.p * (4 if prec == "fp32" else 8)
 
 
 # Files that define the step kernels and their launch parameters (tile
@@ -233,7 +221,7 @@ def time_workload(name, prec, K, W):
     value = cells * steps * K / (total_ms * 1e-3) / 1e6
     step_time_ms = step_ms / (steps * K)
     kernel, spl = step_kernel(P, prec, steps)
-    abytes = alg_bytes_per_cell_step(P, prec)
+    abytes = alg_bytes(P, prec)
     achieved = abytes * cells / (step_time_ms * 1e-3) / 1e9
     two_d = P.dim == 2
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

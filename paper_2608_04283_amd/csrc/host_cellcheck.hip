@@ -213,4 +213,8 @@ void vklb_cc_default_shape(int kind, int prec, long long nx, long long ny, int w
   out[1] = std::min(default_band(kind, p, &g, out[0]), max_band(kind, 2, resolve_basis(0, p, 2)));
   out[2] = default_halo(kind);
 }
+// 1 if a solve keeps U alone.
+int vklb_cc_keeps_u(int kind, int prec, int dim, double omega) {
+  return keeps_u(kind, dim, prec == 8 ? VKLB_FP64 : VKLB_FP32, omega) ? 1 : 0;
+}
 }

@@ -75,12 +75,16 @@ def tune_shapes(precision="fp32", steps=20, seed=11, sizes=TUNE_SIZES):
         pool.close()
 
 
-def _alg_bytes(prob, precision):
-    """Algorithmic bytes of one cell-step: the stored state read once and
-    written once (omega = 1: U, 2 p s; else, and in 1D FP64 shallow water,
-    every population, 2 Q p s)."""
-    u = prob.omega == 1.0 and not (prob.system == "sw" and prob.dim == 1 and precision == "fp64")
-    slots = 1 if u else prob.Q
+def keeps_u(prob, precision):
+    """The library's rule (keeps_u in vklb_host.hpp) for the solves that store U
+    alone: the collision of omega = 1 returns the equilibrium of U."""
+    return prob.omega == 1.0 and not (prob.system == "sw" and prob.dim == 1 and precision == "fp64")
+
+
+def alg_bytes(prob, precision):
+    """Bytes a cell-step cannot do without: the stored state read once and
+    written once (U, 2 p s, or every population, 2 Q p s)."""
+    slots = 1 if keeps_u(prob, precision) else prob.Q
     return 2 * slots * prob.p * (4 if precision == "fp32" else 8)
 
 
@@ -98,7 +102,7 @@ def run_batched(requests, budget_bytes, precision="fp32", chunk_rounds=64, realt
     latencies = []
     results = {}
     cell_steps = 0
-    alg_bytes = 0
+    moved = 0
     n_done = 0
     failed = []
     t0 = time.perf_counter()
@@ -120,7 +124,7 @@ def run_batched(requests, budget_bytes, precision="fp32", chunk_rounds=64, realt
                 t_done = time.perf_counter() - t0
                 latencies.append(t_done - arrival[c["tag"]])
                 cell_steps += c["problem"].cells * c["steps"]
-                alg_bytes += c["problem"].cells * c["steps"] * _alg_bytes(c["problem"], precision)
+                moved += c["problem"].cells * c["steps"] * alg_bytes(c["problem"], precision)
                 n_done += 1
                 if progress and n_done % 200 == 0:
                     progress(n_done, len(reqs))
@@ -138,7 +142,7 @@ def run_batched(requests, budget_bytes, precision="fp32", chunk_rounds=64, realt
     return {"mode": "batched", "solves": n_done, "ok": ok, "makespan_s": makespan, "solves_per_s": ok / makespan,
             "completed_per_s": n_done / makespan,
             "p50_s": p50, "p99_s": p99, "cell_steps": cell_steps, "mcell_steps_per_s": cell_steps / makespan / 1e6,
-            "alg_gb_per_s": alg_bytes / makespan / 1e9,
+            "alg_gb_per_s": moved / makespan / 1e9,
             "nonphysical": len(failed), "failed": failed, "arena_peak_bytes": stats["arena_peak"],
             "rounds": stats["rounds"], "graph_launches": stats["graph_launches"],
             "graph_captures": stats["graph_captures"],
@@ -154,7 +158,7 @@ def run_plain(requests, precision="fp32", realtime=True, keep_results=False, gra
     latencies = []
     results = {}
     cell_steps = 0
-    alg_bytes = 0
+    moved = 0
     failed = []
     t0 = time.perf_counter()
     try:
@@ -179,7 +183,7 @@ def run_plain(requests, precision="fp32", realtime=True, keep_results=False, gra
             t_done = time.perf_counter() - t0
             latencies.append(t_done - (rq.arrival if realtime else 0.0))
             cell_steps += prob.cells * n
-            alg_bytes += prob.cells * n * _alg_bytes(prob, precision)
+            moved += prob.cells * n * alg_bytes(prob, precision)
             if progress and len(latencies) % 100 == 0:
                 progress(len(latencies), len(reqs))
             if keep_results:
@@ -192,7 +196,7 @@ def run_plain(requests, precision="fp32", realtime=True, keep_results=False, gra
     return {"mode": "plain", "solves": len(reqs), "ok": ok, "makespan_s": makespan, "solves_per_s": ok / makespan,
             "completed_per_s": len(reqs) / makespan,
             "p50_s": p50, "p99_s": p99, "cell_steps": cell_steps, "mcell_steps_per_s": cell_steps / makespan / 1e6,
-            "alg_gb_per_s": alg_bytes / makespan / 1e9,
+            "alg_gb_per_s": moved / makespan / 1e9,
             "nonphysical": len(failed), "failed": failed, "results": results if keep_results else None}
 
 

@@ -25,6 +25,7 @@ def cc():
     L.vklb_cc_uband_of.argtypes = [ctypes.c_int, ctypes.c_int]
     L.vklb_cc_default_shape.argtypes = [ctypes.c_int, ctypes.c_int, ll, ll, ctypes.c_int, ctypes.c_void_p]
     L.vklb_cc_default_shape.restype = None
+    L.vklb_cc_keeps_u.argtypes = [ctypes.c_int] * 3 + [ctypes.c_double]
     L.vklb_cc_uwg_lanes.argtypes = [ctypes.c_int, ll, ctypes.c_int]
     return L
 
@@ -124,3 +125,18 @@ def test_the_tuner_times_each_1d_shape_once(cc, omega):
         assert [cc.vklb_cc_uwg_lanes(KIND["euler"], n, k) for k in lanes] == lanes
         assert cc.vklb_cc_uwg_lanes(KIND["euler"], n, 0) in lanes
     assert [c[0] for c in candidates(cc, "euler", 4, 3000, omega=omega)] == ([256] if omega == 1.0 else [256, 512])
+
+
+def test_the_rule_of_the_solves_that_keep_u_is_the_same_in_python(cc):
+    """serving.keeps_u (the algorithmic bytes of the benchmark and of the served
+    stream) states the library's rule."""
+    from paper_2608_04283_amd import inputs as I
+    from paper_2608_04283_amd.serving import alg_bytes, keeps_u
+    for system in KIND:
+        for dim in (1, 2):
+            for prec, size in (("fp32", 4), ("fp64", 8)):
+                for omega in (1.0, 1.0 + 2.0 ** -52, 0.9, 1.5, 2.0):
+                    P = I.Problem(name="p", system=system, dim=dim, n=(8,) * dim, omega=omega)
+                    u = bool(cc.vklb_cc_keeps_u(KIND[system], size, dim, omega))
+                    assert keeps_u(P, prec) == u
+                    assert alg_bytes(P, prec) == 2 * P.p * size * (1 if u else P.Q)
