@@ -10,8 +10,8 @@ launch in one workgroup).
 Headline workload: 2D Euler four-quadrant Riemann data, 2048^2 cells, 2000
 steps, FP32: the largest single-GPU configuration. With omega = 1 a solve keeps
 U alone (67 MB a buffer), and its step is bound by the vector unit rather than
-by HBM; the roofline entry states the bytes it cannot do without against the
-HBM peak all the same. The other configurations run beside it under
+by HBM ("bound"); the roofline entry states the bytes it cannot do without
+against the HBM peak ("roof") all the same. The other configurations run beside it under
 "also" (1D shallow water in both lattice forms, 1D Euler shock tube FP32 and
 FP64, the 1D smooth wave to 65,536 cells, 1D and 2D MHD), and the mixed
 request stream under "serving".
@@ -224,14 +224,20 @@ def time_workload(name, prec, K, W):
     abytes = alg_bytes(P, prec)
     achieved = abytes * cells / (step_time_ms * 1e-3) / 1e9
     two_d = P.dim == 2
-    roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    # what bounds the step (counters: profiles/); achieved, peak and frac are of HBM whatever does
+    if two_d:
+        bound = "vector unit" if keeps_u(P, prec) else "hbm"
+    else:
+        bound = "launch latency" if spl == 1 else "one compute unit"
+    roof = {"bound": bound, "roof": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": profiled_traffic(name, prec),
             "kernel": kernel, "avg_launch_us": round(step_time_ms * spl * 1e3, 3), "steps_per_launch": spl,
             "us_per_step": round(step_time_ms * 1e3, 3), "alg_bytes_per_cell_step": abytes,
             "cells_per_launch": cells, "populations_mb": round(abytes * cells / 1e6, 1)}
     if not two_d:
-        roof["note"] = ("working set cache-resident between steps: the step is bound by the latency of one "
-                        "dependent launch, not by HBM")
+        roof["note"] = "working set cache-resident between steps: the step is bound by " + (
+            "the latency of one dependent launch, not by HBM" if spl == 1 else
+            "the arithmetic and barriers of one workgroup, not by HBM")
     out = {"workload": P.name, "value": value, "ms_per_solve": total_ms / K, "steps_per_solve": steps,
            "error": error_vs_oracle(name, prec, U_final), "exact": error_vs_exact(name, P, U_final, t_end),
            "cells": cells, "t_end": t_end, "roofline": roof, "dtype": "f32" if prec == "fp32" else "f64",
