@@ -441,22 +441,20 @@ __device__ inline void ustep1d_tile(const SolveDesc& sd, int tile) {
       a1[v] = s_plus[v][pos - 1];
       a2[v] = s_minus[v][pos + 1];
     }
-    {
-      if (charbc && (x == 0 || x == N - 1)) {
-        T e0[P], e1[P], e2[P];
-        uchar_state<KIND, T, BASIS>(sd, U, s_unb[x == 0 ? 0 : 1], x != 0, ixi, Lam, ch, Un, e0, e1, e2);
+    if (charbc && (x == 0 || x == N - 1)) {
+      T e0[P], e1[P], e2[P];
+      uchar_state<KIND, T, BASIS>(sd, U, s_unb[x == 0 ? 0 : 1], x != 0, ixi, Lam, ch, Un, e0, e1, e2);
 #pragma unroll
-        for (int v = 0; v < P; ++v) lo_new[v] = T(0);
-      } else {
-        uadvance1d<KIND, T, BASIS>(sd, pr, ixi, U, lo, fp, fm, net, a1, a2, Un, lo_new);
-      }
-#pragma unroll
-      for (int v = 0; v < P; ++v) {
-        dst[x + (long long)v * sd.us] = Un[v];
-        if (K::COMP) dst[x + (long long)(P + v) * sd.us] = lo_new[v];
-      }
-      K::new_state(sd, Un, x, n + 1, lam, cfm);
+      for (int v = 0; v < P; ++v) lo_new[v] = T(0);
+    } else {
+      uadvance1d<KIND, T, BASIS>(sd, pr, ixi, U, lo, fp, fm, net, a1, a2, Un, lo_new);
     }
+#pragma unroll
+    for (int v = 0; v < P; ++v) {
+      dst[x + (long long)v * sd.us] = Un[v];
+      if (K::COMP) dst[x + (long long)(P + v) * sd.us] = lo_new[v];
+    }
+    K::new_state(sd, Un, x, n + 1, lam, cfm);
   }
   block_max2<MHD>(lam, cfm, red_end, B);
   end_step(sd, S, tile, lam, cfm);
@@ -467,11 +465,11 @@ __global__ void __launch_bounds__(ulanes1d(SIDE)) k_ustep1d(const SolveDesc sd) 
   ustep1d_tile<KIND, T, BASIS, CHARBC, SIDE>(sd, blockIdx.x);
 }
 
-// Largest grid that runs in one workgroup, [MHD][FP64]: where a step there
-// still takes less than a launch. us per step, one workgroup / a launch each:
-// Euler FP32 2000 cells 2.95 / 3.4, 2500 3.24 / 3.4; FP64 1000 3.23 / 3.8, 1500
-// 4.10 / 3.9; shallow water FP32 2000 2.38 / 3.4; MHD FP32 700 4.3 / 5.4, 1000
-// 5.5 / 5.5; FP64 500 5.4 / 7.6 (more lanes would spill).
+// Largest grid that runs in one workgroup, [MHD][FP64]: what its kernels hold
+// at two cells a lane (MHD and FP64: as many registers as spill beyond), and
+// where a step still takes less than a launch. us per step at the limit, one
+// workgroup / a launch each: FP32 Euler 2.88 / 3.14, shallow water 2.38 / 2.93,
+// MHD 4.18 / 4.69; FP64 Euler 2.98 / 3.35, MHD 5.35 / 5.74.
 constexpr int kUWgMax[2][2] = {{2048, 1024}, {768, 512}};
 
 // Max over the wavefront, in every lane, of non-negative values (negatives
