@@ -114,6 +114,7 @@ struct Req {
   size_t off = 0;
   SolveDesc sd;
   int slot = -1;
+  long long round0 = 0;  // the pool's round at admission
 };
 
 struct SlotStatus {
@@ -258,6 +259,7 @@ vklb_status admit(vklb_pool* p) {
     r->sd = make_desc(p->base + off, r->L, &r->sys, &r->grid, &r->speed, r->omega, r->bc, &r->eq, width, r->band,
                       r->halo, true);
     r->sd.pop = nullptr;  // the pool takes no checkpoints
+    r->round0 = p->round;
     r->sd.npar = int(p->round & 1);  // step 0 runs at the parity of the next round
     if (r->sd.nblocks > kFoldAbove) r->sd.nred = 1;  // as a single solve: partials folded after each round
     // initialization into the parity of the next round
@@ -288,6 +290,15 @@ vklb_status admit(vklb_pool* p) {
     for (Req* r : admitted) std::vector<double>().swap(r->U0);
   }
   return VKLB_OK;
+}
+
+// Rounds that class c still needs: a round is a step at most, so none once
+// every resident solve has had its max_steps rounds.
+long long rounds_left(const vklb_pool* p, int c) {
+  long long left = 0;
+  for (const Req* r : p->slots)
+    if (r && r->cls == c) left = std::max(left, r->max_steps - (p->round - r->round0));
+  return left;
 }
 
 vklb_status upload_lists(vklb_pool* p) {
@@ -443,12 +454,21 @@ vklb_status vklb_pool_run(vklb_pool* p, int rounds) {
     if (!p->nwork[c]) continue;
     if (!p->cls_stream[c]) PCHK(p, hipStreamCreateWithFlags(&p->cls_stream[c], hipStreamNonBlocking));
     if (!p->ev_cls[c]) PCHK(p, hipEventCreateWithFlags(&p->ev_cls[c], hipEventDisableTiming));
+    // Only the rounds the class needs, and one more where the parity of its
+    // scalars has to end at that of the whole chunk. Rounds after the last
+    // step, and graphs replayed once, cost pools whose solves of one kind are
+    // two classes (omega = 1 and others) more than keeping U saved: 6 small 1D
+    // solves of mixed omega 3.8 ms, 3.5 with the classes as one, 3.6 with both gone.
+    const long long left = rounds_left(p, c);
+    const int count = left >= rounds ? rounds : int(left) + int((rounds - left) & 1);
+    if (count == 0) continue;
     hipStream_t cs = p->cls_stream[c];
     PCHK(p, hipStreamWaitEvent(cs, p->ev_main, 0));
-    if (p->gexec[c] && (p->graph_rounds[c] != rounds || p->graph_par[c] != par0)) drop_class_graph(p, c);
+    if (p->gexec[c] && (p->graph_rounds[c] != count || p->graph_par[c] != par0)) drop_class_graph(p, c);
     // a class whose resident set was the same at the previous call is captured
-    // once (this call) and replayed while it stays the same
-    const bool capture = !p->gexec[c] && p->stable_calls[c] >= 1;
+    // once (this call) and replayed while it stays the same, if at least one
+    // more whole chunk is to come
+    const bool capture = !p->gexec[c] && p->stable_calls[c] >= 1 && left >= 2ll * rounds;
     if (capture) {
       PCHK(p, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     }
@@ -458,7 +478,7 @@ vklb_status vklb_pool_run(vklb_pool* p, int rounds) {
         if (p->slots[i] && p->slots[i]->cls == c && p->slots[i]->sd.nred != p->slots[i]->sd.nblocks)
           fold.push_back(&p->slots[i]->sd);
       hipError_t e = hipSuccess;
-      for (int k = 0; k < rounds && e == hipSuccess; ++k) {
+      for (int k = 0; k < count && e == hipSuccess; ++k) {
         const int par = (par0 + k) & 1;
         e = p->cls_launch[c].batched(p->d_descs, p->d_work[c], p->d_nwork + c, par, p->nwork[c], cs);
         for (const SolveDesc* d : fold)
