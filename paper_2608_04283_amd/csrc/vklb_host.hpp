@@ -158,12 +158,11 @@ inline bool keeps_u(int kind, int dim, vklb_precision prec, double omega) {
 inline long long ustep_waves(const vklb_grid* g, int band) {
   return ((g->n[0] + 63) / 64) * ((g->n[1] + band - 1) / band);
 }
-// 1D: tiles of 256 cells (a fifth wavefront for the sides) where they make a
-// whole number of workgroups per compute unit, of up to `most`, and tiles of
-// 254 make one more on a few units, which the others wait for. Beyond, the
-// units no longer work in step, and the fifth wavefront costs more than the
-// 0.8 % of tiles it saves: from two workgroups a unit on for FP64 MHD (its
-// registers), three for FP32 MHD, eight for the others. us per step with tiles
+// 1D: tiles of 256 cells (a fifth wavefront for the sides) where they need at
+// most `most` workgroups per compute unit and tiles of 254 one more on a few
+// units, which the others wait for. With more workgroups a unit the fifth
+// wavefront costs more than the 0.8 % of tiles it saves: from two on for FP64
+// MHD (its registers), three for FP32 MHD, eight for the others. us per step with tiles
 // of 254 / 256 on MI355X: Euler FP32 65,536 cells 3.68 / 3.61, 131,072 4.56 / 4.38,
 // 262,144 6.38 / 5.87, 524,288 10.8 / 11.2, 2^20 15.5 / 17.4, 2^24 194 / 236; FP64
 // 65,536 4.18 / 3.94, 262,144 7.27 / 7.19, 2^20 18.5 / 22.3; shallow water FP32

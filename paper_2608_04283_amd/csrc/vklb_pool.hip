@@ -292,13 +292,12 @@ vklb_status admit(vklb_pool* p) {
   return VKLB_OK;
 }
 
-// Rounds that class c still needs: a round is a step at most, so none once
+// Rounds that each class still needs: a round is a step at most, so none once
 // every resident solve has had its max_steps rounds.
-long long rounds_left(const vklb_pool* p, int c) {
-  long long left = 0;
+void rounds_left(const vklb_pool* p, long long (&left)[kClasses]) {
+  for (long long& l : left) l = 0;
   for (const Req* r : p->slots)
-    if (r && r->cls == c) left = std::max(left, r->max_steps - (p->round - r->round0));
-  return left;
+    if (r) left[r->cls] = std::max(left[r->cls], r->max_steps - (p->round - r->round0));
 }
 
 vklb_status upload_lists(vklb_pool* p) {
@@ -443,6 +442,8 @@ vklb_status vklb_pool_run(vklb_pool* p, int rounds) {
     return (long long)p->nwork[c] * ((c >> 1) & 1 ? 4 : 1) * ((c >> 2) == K_MHD ? 4 : 1);
   };
   std::stable_sort(order, order + kClasses, [&](int a, int b) { return cost(a) > cost(b); });
+  long long left[kClasses];
+  rounds_left(p, left);
   for (int c : order) {
     if (p->changed[c]) {
       drop_class_graph(p, c);
@@ -459,8 +460,7 @@ vklb_status vklb_pool_run(vklb_pool* p, int rounds) {
     // step, and graphs replayed once, cost pools whose solves of one kind are
     // two classes (omega = 1 and others) more than keeping U saved: 6 small 1D
     // solves of mixed omega 3.8 ms, 3.5 with the classes as one, 3.6 with both gone.
-    const long long left = rounds_left(p, c);
-    const int count = left >= rounds ? rounds : int(left) + int((rounds - left) & 1);
+    const int count = left[c] >= rounds ? rounds : int(left[c]) + int((rounds - left[c]) & 1);
     if (count == 0) continue;
     hipStream_t cs = p->cls_stream[c];
     PCHK(p, hipStreamWaitEvent(cs, p->ev_main, 0));
@@ -468,7 +468,7 @@ vklb_status vklb_pool_run(vklb_pool* p, int rounds) {
     // a class whose resident set was the same at the previous call is captured
     // once (this call) and replayed while it stays the same, if at least one
     // more whole chunk is to come
-    const bool capture = !p->gexec[c] && p->stable_calls[c] >= 1 && left >= 2ll * rounds;
+    const bool capture = !p->gexec[c] && p->stable_calls[c] >= 1 && left[c] >= 2ll * rounds;
     if (capture) {
       PCHK(p, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     }
